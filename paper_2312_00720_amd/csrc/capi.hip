@@ -30,6 +30,18 @@ void check_col(const gj_col &c, int64_t n, const char *what) {
     gj::require(n == 0 || c.data != nullptr, std::string(what) + ": null data");
 }
 
+// Chunk rows of the partition group-by's pass: the key and, unless only row ids
+// move (gfur), the value columns.
+uint32_t gb_chunk_rows(uint32_t n, int kb, int n_vals, const int *width, bool gfur) {
+    uint32_t row = (uint32_t)kb + (gfur ? 4u : 0u);
+    bool narrow = kb == 4;
+    for (int i = 0; i < n_vals && !gfur; ++i) {
+        row += (uint32_t)width[i];
+        narrow = narrow && width[i] == 4;
+    }
+    return gj::pass_chunk_rows(n, row, narrow);
+}
+
 void check_rel(const gj_rel *r, const char *what) {
     gj::require(r != nullptr, std::string(what) + ": null relation");
     gj::require(r->n_rows >= 0, std::string(what) + ": negative row count");
@@ -427,9 +439,10 @@ int gj_groupby(gj_col key, const gj_col *vals, int32_t n_vals, int64_t n_rows, c
         // histogram from the same read of the keys
         const uint32_t *hist8 = nullptr;
         const bool want_hist = algo == GJ_GB_AUTO || (algo == GJ_GB_PARTITION && o.radix_bits == 0);
+        const uint32_t chunk_rows = gb_chunk_rows(n, kb, vcols.n, vcols.width, gfur);
         if (algo == GJ_GB_AUTO || algo == GJ_GB_HASH || algo == GJ_GB_SORT_DE ||
             (algo == GJ_GB_PARTITION && o.radix_bits == 0))
-            g_est = gj::estimate_groups(ctx, kb, key.data, n, &varying, want_hist ? &hist8 : nullptr);
+            g_est = gj::estimate_groups(ctx, kb, key.data, n, &varying, want_hist ? &hist8 : nullptr, chunk_rows);
         if (algo == GJ_GB_AUTO) {
             float f[12];
             gj::features_groupby(f, (double)n, kb, n_vals, g_est, varying, o.skew_hint,
@@ -542,7 +555,8 @@ int gj_groupby_features(gj_col key, const gj_col *vals, int32_t n_vals, const gj
         const bool want_hist = o.algo == GJ_GB_AUTO || (o.algo == GJ_GB_PARTITION && o.radix_bits == 0);
         const uint32_t *hist8 = nullptr;
         const double g_est =
-            gj::estimate_groups(ctx, kb, key.data, (uint32_t)n_rows, &varying, want_hist ? &hist8 : nullptr);
+            gj::estimate_groups(ctx, kb, key.data, (uint32_t)n_rows, &varying, want_hist ? &hist8 : nullptr,
+                                gb_chunk_rows((uint32_t)n_rows, kb, n_vals, vw, o.mat == GJ_MAT_GFUR));
         gj::features_groupby(features, (double)n_rows, kb, n_vals, g_est, varying, o.skew_hint,
                              (double)gj::hgb_record_bytes(aggs, n_aggs, vw));
         return GJ_OK;

@@ -646,18 +646,18 @@ __device__ __forceinline__ void hll_keys(const K (&k)[U], uint32_t valid, uint32
         if ((ir[u] >> 16) > cur[u]) atomicMax(&s_reg[ir[u] & 0xFFFFu], ir[u] >> 16);
 }
 
-template <typename K, bool HIST>
-__global__ __launch_bounds__(kBlock) void k_hll(const K *__restrict__ keys, uint32_t n, uint32_t *__restrict__ regs,
+template <typename K, bool HIST, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_hll(const K *__restrict__ keys, uint32_t n, uint32_t *__restrict__ regs,
                                                 unsigned long long *__restrict__ bits, uint32_t chunk_rows,
                                                 uint32_t *__restrict__ hist8) {
     constexpr int U = sizeof(K) == 4 ? 16 : 8;  // keys per thread and round
     constexpr int V = 16 / (int)sizeof(K);  // keys per 16-byte load
     using B = std::conditional_t<sizeof(K) == 4, uint32_t, unsigned long long>;
     __shared__ uint32_t s_reg[1 << kHllBits];
-    __shared__ uint32_t s_cnt[HIST ? kWaves : 1][HIST ? 256 : 1];
-    for (int i = threadIdx.x; i < (1 << kHllBits); i += kBlock) s_reg[i] = 0;
+    __shared__ uint32_t s_cnt[HIST ? BLOCK / kWave : 1][HIST ? 256 : 1];
+    for (int i = threadIdx.x; i < (1 << kHllBits); i += BLOCK) s_reg[i] = 0;
     if constexpr (HIST)
-        for (int i = threadIdx.x; i < kWaves * 256; i += kBlock) (&s_cnt[0][0])[i] = 0;
+        for (int i = threadIdx.x; i < (BLOCK / kWave) * 256; i += BLOCK) (&s_cnt[0][0])[i] = 0;
     __syncthreads();
     B o = 0, x = ~B(0);
     uint32_t *cnt = &s_cnt[HIST ? threadIdx.x / kWave : 0][0];
@@ -665,21 +665,21 @@ __global__ __launch_bounds__(kBlock) void k_hll(const K *__restrict__ keys, uint
     if constexpr (HIST) {
         lo = blockIdx.x * chunk_rows;
         hi = (uint32_t)min<uint64_t>((uint64_t)lo + chunk_rows, n);
-        stride = kBlock * U;
+        stride = BLOCK * U;
     } else {
-        lo = blockIdx.x * kBlock * U;
+        lo = blockIdx.x * BLOCK * U;
         hi = n;
-        stride = gridDim.x * kBlock * U;
+        stride = gridDim.x * BLOCK * U;
     }
     uint32_t base = lo;
     if ((reinterpret_cast<uintptr_t>(keys) & 15u) == 0) {
         // whole rounds: a wave's 16-byte loads cover 1 KB of consecutive keys
-        // (rounds start at multiples of kBlock * U rows, so every load is aligned)
-        for (; (uint64_t)base + kBlock * U <= hi; base += stride) {
+        // (rounds start at multiples of BLOCK * U rows, so every load is aligned)
+        for (; (uint64_t)base + BLOCK * U <= hi; base += stride) {
             const uint4 *__restrict__ q = reinterpret_cast<const uint4 *>(keys + base) + threadIdx.x;
             uint4 v[U / V];
 #pragma unroll
-            for (int j = 0; j < U / V; ++j) v[j] = q[j * kBlock];
+            for (int j = 0; j < U / V; ++j) v[j] = q[j * BLOCK];
             // the keys in two halves keep the register count down
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
@@ -699,7 +699,7 @@ __global__ __launch_bounds__(kBlock) void k_hll(const K *__restrict__ keys, uint
             uint32_t valid = 0;
 #pragma unroll
             for (int u = 0; u < U / 2; ++u) {
-                const uint32_t i = base + (half * (U / 2) + u) * kBlock + threadIdx.x;
+                const uint32_t i = base + (half * (U / 2) + u) * BLOCK + threadIdx.x;
                 k[u] = i < hi ? keys[i] : K(0);
                 valid |= (i < hi ? 1u : 0u) << u;
             }
@@ -716,13 +716,13 @@ __global__ __launch_bounds__(kBlock) void k_hll(const K *__restrict__ keys, uint
         atomicAnd(&bits[1], (unsigned long long)x | (sizeof(K) == 4 ? 0xFFFFFFFF00000000ull : 0ull));
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < (1 << kHllBits); i += kBlock)
+    for (int i = threadIdx.x; i < (1 << kHllBits); i += BLOCK)
         if (s_reg[i]) atomicMax(&regs[i], s_reg[i]);
     if constexpr (HIST) {
-        for (int d = threadIdx.x; d < 256; d += kBlock) {
+        for (int d = threadIdx.x; d < 256; d += BLOCK) {
             uint32_t t = 0;
 #pragma unroll
-            for (int q = 0; q < kWaves; ++q) t += s_cnt[q][d];
+            for (int q = 0; q < (BLOCK / kWave); ++q) t += s_cnt[q][d];
             hist8[(size_t)blockIdx.x * 256u + d] = t;
         }
     }
@@ -2216,7 +2216,7 @@ size_t hgb_record_bytes(const gj_agg *aggs, int n_aggs, const int *val_w) {
 }
 
 double estimate_groups(Ctx &ctx, int key_bytes, const void *key, uint32_t n, int *varying_bytes,
-                       const uint32_t **hist8) {
+                       const uint32_t **hist8, uint32_t chunk_rows) {
     if (varying_bytes) *varying_bytes = 0;
     if (hist8) *hist8 = nullptr;
     if (n == 0) return 0.0;
@@ -2228,22 +2228,27 @@ double estimate_groups(Ctx &ctx, int key_bytes, const void *key, uint32_t n, int
     fill_u32(st, regs + m + 2, 0xFFFFFFFFu, 2);
     if (hist8) {
         // one workgroup per chunk of the partition pass that may follow
-        const uint32_t crows = pass_chunk_rows(n), chunks = ceil_div_u32(n, crows);
+        const uint32_t crows = chunk_rows, chunks = ceil_div_u32(n, crows);
         uint32_t *h8 = ctx.scratch_n<uint32_t>((size_t)chunks * 256);
         *hist8 = h8;
-        if (key_bytes == 4)
-            GJ_LAUNCH("k_hll", 4.0 * n, (k_hll<int32_t, true>), dim3(chunks), dim3(kBlock), 0, st,
-                      static_cast<const int32_t *>(key), n, regs, bits, crows, h8);
-        else
-            GJ_LAUNCH("k_hll", 8.0 * n, (k_hll<int64_t, true>), dim3(chunks), dim3(kBlock), 0, st,
-                      static_cast<const int64_t *>(key), n, regs, bits, crows, h8);
+#define GJ_HLL(K, BLOCK)                                                                                       \
+    GJ_LAUNCH("k_hll", (double)n * sizeof(K), (k_hll<K, true, BLOCK>), dim3(chunks), dim3(BLOCK), 0, st,       \
+              static_cast<const K *>(key), n, regs, bits, crows, h8)
+        if (crows >= (1u << 16)) {  // long chunks: few of them must fill the chip
+            if (key_bytes == 4) GJ_HLL(int32_t, 1024);
+            else GJ_HLL(int64_t, 1024);
+        } else {
+            if (key_bytes == 4) GJ_HLL(int32_t, kBlock);
+            else GJ_HLL(int64_t, kBlock);
+        }
+#undef GJ_HLL
     } else {
         const uint32_t grid = std::max<uint32_t>(1, std::min<uint32_t>(ceil_div_u32(n, kBlock * 16), 2048));
         if (key_bytes == 4)
-            GJ_LAUNCH("k_hll", 4.0 * n, (k_hll<int32_t, false>), dim3(grid), dim3(kBlock), 0, st,
+            GJ_LAUNCH("k_hll", 4.0 * n, (k_hll<int32_t, false, kBlock>), dim3(grid), dim3(kBlock), 0, st,
                       static_cast<const int32_t *>(key), n, regs, bits, 0u, nullptr);
         else
-            GJ_LAUNCH("k_hll", 8.0 * n, (k_hll<int64_t, false>), dim3(grid), dim3(kBlock), 0, st,
+            GJ_LAUNCH("k_hll", 8.0 * n, (k_hll<int64_t, false, kBlock>), dim3(grid), dim3(kBlock), 0, st,
                       static_cast<const int64_t *>(key), n, regs, bits, 0u, nullptr);
     }
     std::vector<uint32_t> h(m + 4);

@@ -27,11 +27,12 @@
 namespace gj {
 namespace {
 
-// Default scatter shape: the wide kernel (1024 threads x 16 rows, one column at
-// a time with a rolling prefetch); group 0 names it among the shapes.
+// Default scatter shape: 1024 threads x 16 rows, the whole-line kernel for large
+// passes (long_chunks) and the wide kernel (one column at a time with a rolling
+// prefetch) otherwise; group 0 names the wide kernel among the shapes.
 constexpr int kScatterBlock = 1024;
 constexpr int kItems = 16;
-constexpr int kGroup = 0;
+constexpr int kGroup = -1;
 constexpr uint32_t kTile = kBlock * kItems;
 
 struct PassArgs {
@@ -49,9 +50,11 @@ struct PassArgs {
     uint32_t nseg;
     const uint32_t *chunk_base;  // nseg + 1 chunk offsets
     uint32_t chunk_rows;
+    int cells;  // long chunks (below): cut at multiples of chunk_rows of the whole input
     uint32_t *hist;  // [chunks][2^bits], laid out as (segment, digit, chunk)
     uint32_t n_rows; // rows of the output columns; every store is checked against it
     const uint8_t *seg_bits;  // optional: digit bits per segment (<= bits; batches of instances)
+    uint32_t row_bytes;       // k_scatter_lines: bytes of the key and every column
 };
 
 // The digit function of the segment a chunk belongs to.
@@ -61,10 +64,51 @@ __device__ __forceinline__ DigitFn seg_digit(const PassArgs &a, uint32_t seg) {
     return d;
 }
 
+// Chunks. Short ones: each segment is cut into pieces of chunk_rows rows, one
+// workgroup each. Long ones (cells): the input is cut at multiples of chunk_rows
+// into as many cells as there are workgroups and at the segments' ends; a
+// workgroup takes the chunks of its cell one by one, so that every workgroup
+// moves the same number of rows whatever the segments' sizes. (One workgroup per
+// chunk of 2^20 rows: segments of 2^21 +- 2000 rows left a few chunks for a
+// second round, 3.3 ms instead of 2.2 at 2^28 rows.)
 struct ChunkLoc {
     uint32_t seg, j, m, row0, row1, hbase;
     int ok;
 };
+
+__device__ __forceinline__ uint32_t seg_chunks(uint32_t s0, uint32_t s1, uint32_t base, uint32_t chunk_rows, int cells) {
+    if (s0 >= s1) return 0u;
+    return cells ? (s1 - 1 - base) / chunk_rows - (s0 - base) / chunk_rows + 1 : ceil_div_u32(s1 - s0, chunk_rows);
+}
+
+// Uniform values in scalar registers (the loads they come from are vector ones).
+__device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// Segment `seg` of cell `cell`: its chunk there.
+__device__ __forceinline__ ChunkLoc cell_chunk(const PassArgs &a, uint32_t cell, uint32_t seg) {
+    ChunkLoc L{};
+    const uint32_t base = uni(a.seg_off[0]), s0 = uni(a.seg_off[seg]), s1 = uni(a.seg_off[seg + 1]);
+    const uint32_t cb = uni(a.chunk_base[seg]), c0 = base + cell * a.chunk_rows;
+    L.seg = seg;
+    L.j = cell - (s0 - base) / a.chunk_rows;
+    L.m = uni(a.chunk_base[seg + 1]) - cb;
+    L.row0 = max(s0, c0);
+    L.row1 = min(s1, c0 + a.chunk_rows);
+    L.hbase = cb << a.bits;
+    L.ok = 1;
+    return L;
+}
+// First segment with rows at or past the cell's first row.
+__device__ uint32_t cell_first_seg(const PassArgs &a, uint32_t cell) {
+    const uint32_t row = a.seg_off[0] + cell * a.chunk_rows;
+    uint32_t lo = 0, hi = a.nseg;  // seg_off[hi] > row
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (a.seg_off[mid] <= row) lo = mid;
+        else hi = mid;
+    }
+    return uni(lo);
+}
 
 __device__ ChunkLoc locate_chunk(const PassArgs &a, uint32_t c) {
     ChunkLoc L{};
@@ -80,6 +124,7 @@ __device__ ChunkLoc locate_chunk(const PassArgs &a, uint32_t c) {
         else hi = mid;
     }
     const uint32_t cb = a.chunk_base[lo];
+    if (a.cells) return cell_chunk(a, (a.seg_off[lo] - a.seg_off[0]) / a.chunk_rows + (c - cb), lo);
     L.seg = lo;
     L.j = c - cb;
     L.m = a.chunk_base[lo + 1] - cb;
@@ -92,13 +137,13 @@ __device__ ChunkLoc locate_chunk(const PassArgs &a, uint32_t c) {
 }
 
 __global__ __launch_bounds__(kBlock) void k_chunk_table(const uint32_t *__restrict__ seg_off,
-                                                        uint32_t nseg, uint32_t chunk_rows,
+                                                        uint32_t nseg, uint32_t chunk_rows, int cells,
                                                         uint32_t *__restrict__ chunk_base) {
     __shared__ uint32_t s_tmp[kWaves];
     uint32_t carry = 0;
     for (uint32_t base = 0; base < nseg; base += kBlock) {
         const uint32_t s = base + threadIdx.x;
-        const uint32_t cnt = s < nseg ? ceil_div_u32(seg_off[s + 1] - seg_off[s], chunk_rows) : 0u;
+        const uint32_t cnt = s < nseg ? seg_chunks(seg_off[s], seg_off[s + 1], seg_off[0], chunk_rows, cells) : 0u;
         uint32_t tot;
         const uint32_t ex = block_exclusive_sum<uint32_t>(cnt, s_tmp, &tot);
         if (s < nseg) chunk_base[s] = carry + ex;
@@ -107,39 +152,59 @@ __global__ __launch_bounds__(kBlock) void k_chunk_table(const uint32_t *__restri
     if (threadIdx.x == 0) chunk_base[nseg] = carry;
 }
 
-template <typename K>
-__global__ __launch_bounds__(kBlock) void k_hist(PassArgs a) {
+// Counts of one chunk's rows per digit.
+template <typename K, int BLOCK>
+__device__ __forceinline__ void hist_chunk(const PassArgs &a, const ChunkLoc &L, uint32_t (*s_cnt)[kRadix]) {
     constexpr int U = 16;  // loads in flight per thread
-    __shared__ uint32_t s_cnt[kWaves][kRadix];
-    __shared__ ChunkLoc s_loc;
-    if (threadIdx.x == 0) s_loc = locate_chunk(a, blockIdx.x);
-    for (int i = threadIdx.x; i < kWaves * kRadix; i += kBlock) (&s_cnt[0][0])[i] = 0;
+    constexpr int W = BLOCK / kWave;
+    for (int i = threadIdx.x; i < W * kRadix; i += BLOCK) (&s_cnt[0][0])[i] = 0;
     __syncthreads();
-    const ChunkLoc L = s_loc;
-    if (!L.ok) return;
     const K *__restrict__ keys = static_cast<const K *>(a.key_in);
     const int tid = threadIdx.x, w = tid / kWave;
     const DigitFn dig = seg_digit(a, L.seg);
-    for (uint32_t base = L.row0; base < L.row1; base += kBlock * U) {
+    for (uint32_t base = L.row0; base < L.row1; base += BLOCK * U) {
         K k[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t row = base + u * kBlock + tid;
+            const uint32_t row = base + u * BLOCK + tid;
             k[u] = row < L.row1 ? keys[row] : K(0);
         }
         // counting needs no order, so plain LDS atomics into the wave's own histogram
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (base + u * kBlock + tid < L.row1) atomicAdd(&s_cnt[w][digit_of<K>(k[u], dig)], 1u);
+            if (base + u * BLOCK + tid < L.row1) atomicAdd(&s_cnt[w][digit_of<K>(k[u], dig)], 1u);
         }
     }
     __syncthreads();
     const uint32_t R = 1u << a.bits;
-    for (uint32_t d = threadIdx.x; d < R; d += kBlock) {
+    for (uint32_t d = threadIdx.x; d < R; d += BLOCK) {
         uint32_t t = 0;
 #pragma unroll
-        for (int q = 0; q < kWaves; ++q) t += s_cnt[q][d];
+        for (int q = 0; q < W; ++q) t += s_cnt[q][d];
         a.hist[L.hbase + d * L.m + L.j] = t;
+    }
+}
+
+template <typename K>
+__global__ __launch_bounds__(kBlock) void k_hist(PassArgs a) {
+    __shared__ uint32_t s_cnt[kWaves][kRadix];
+    __shared__ ChunkLoc s_loc;
+    if (threadIdx.x == 0) s_loc = locate_chunk(a, blockIdx.x);
+    __syncthreads();
+    if (s_loc.ok) hist_chunk<K, kBlock>(a, s_loc, s_cnt);
+}
+
+// Long chunks: a workgroup per cell; 1024 threads, since there are only about as
+// many cells as compute units.
+template <typename K>
+__global__ __launch_bounds__(1024) void k_hist_cells(PassArgs a) {
+    __shared__ uint32_t s_cnt[1024 / kWave][kRadix];
+    const uint32_t end = uni(a.seg_off[0]) + min((blockIdx.x + 1) * a.chunk_rows, a.n_rows);
+    for (uint32_t seg = cell_first_seg(a, blockIdx.x); seg < a.nseg && uni(a.seg_off[seg]) < end; ++seg) {
+        const ChunkLoc L = cell_chunk(a, blockIdx.x, seg);
+        if (L.row0 >= L.row1) continue;
+        hist_chunk<K, 1024>(a, L, s_cnt);
+        __syncthreads();
     }
 }
 
@@ -575,6 +640,406 @@ __global__ __launch_bounds__(BLOCK) void k_scatter_wide(PassArgs a) {
     if (nt) scatter_tile_wide<K, BLOCK, ITEMS, false>(a, dig, S, s_buf, tile0, nt, key, v, 0u, 0u);
 }
 
+// Whole-line scatter. What bounds the scatter is not how long a tile's run of a
+// digit is but whether its two ends share 128-byte lines with other runs: with
+// 512-byte runs a write probe moves 5.2 TB/s where they start on a line and 4.1
+// where they start anywhere (128-byte runs: 5.1 against 2.8). So this kernel
+// writes whole lines of A rows only: a digit's rows past its last full line stay
+// in LDS (the carry, one line per digit and column) until a later tile of the
+// chunk completes it. Only a chunk's first and last line of each digit are
+// written in parts, so chunks are long (several tiles).
+//
+// Per tile: ranks as in the wide kernel; then, one column at a time, the carried
+// rows of every digit with a full line move to the front of the digit's lines in
+// the stage, the tile's rows go to their place behind them (or, past the last
+// full line, into the carry), and the staged lines leave in 16-byte accesses.
+struct LineLds {
+    uint8_t *stage;   // the full lines of one column, then the carry of every column (key first)
+    uint16_t *wcnt;   // [waves][D]: rows per wave and digit, then their exclusive prefix
+    uint32_t *info;   // per digit: stage place of its next new row | end of its lines << 16
+    uint4 *pos;       // per digit: output row before and after this tile, first row of the chunk, row of (line 0, value 0)
+    uint16_t *lbase;  // first line per digit, D + 1
+    uint8_t *tab;     // digit of every line
+    uint32_t *tmp;
+};
+constexpr size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
+constexpr int kLineWaves = 16;
+constexpr uint32_t line_max(uint32_t D, uint32_t A, uint32_t tile) { return (tile + D * (A - 1)) / A + 1; }  // full lines of a tile, and a spare one
+// LDS bytes of a pass: D digits, row_bytes per row (key and columns), w bytes of the widest column.
+constexpr size_t line_lds_bytes(uint32_t D, uint32_t A, uint32_t row_bytes, uint32_t tile, uint32_t w) {
+    return (size_t)line_max(D, A, tile) * A * w + (size_t)D * A * row_bytes + align16((size_t)kLineWaves * D * 2) +
+           align16((size_t)D * 4) + (size_t)D * 16 + align16((size_t)(D + 1) * 2) + align16(line_max(D, A, tile)) +
+           4 * kLineWaves;
+}
+__device__ __forceinline__ LineLds line_lds(uint8_t *p, uint32_t D, uint32_t A, uint32_t row_bytes, uint32_t tile,
+                                            uint32_t w) {
+    LineLds S;
+    S.stage = p;
+    p += (size_t)line_max(D, A, tile) * A * w + (size_t)D * A * row_bytes;
+    S.pos = reinterpret_cast<uint4 *>(p);
+    p += (size_t)D * 16;
+    S.wcnt = reinterpret_cast<uint16_t *>(p);
+    p += align16((size_t)kLineWaves * D * 2);
+    S.info = reinterpret_cast<uint32_t *>(p);
+    p += align16((size_t)D * 4);
+    S.lbase = reinterpret_cast<uint16_t *>(p);
+    p += align16((size_t)(D + 1) * 2);
+    S.tab = p;
+    p += align16(line_max(D, A, tile));
+    S.tmp = reinterpret_cast<uint32_t *>(p);
+    return S;
+}
+
+// Lanes of the wave with this lane's digit of at most B bits (bits past the
+// digit's are equal in all lanes). Four vector instructions a bit.
+template <int B>
+__device__ __forceinline__ uint64_t match_digit(uint32_t d) {
+    uint32_t lo = 0, hi = 0;  // lanes that differ
+#pragma unroll
+    for (int k = 0; k < B; ++k) {
+        uint32_t s = (uint32_t)__builtin_amdgcn_sbfe((int)d, k, 1);
+        asm("" : "+v"(s));  // the ballot compares this value; no second shift
+        const uint64_t bk = __ballot(s != 0);
+        lo |= (uint32_t)bk ^ s;
+        hi |= (uint32_t)(bk >> 32) ^ s;
+    }
+    return ~((uint64_t)hi << 32 | lo);
+}
+
+// Stable ranks of the wave's rows among its rows of the same digit, in input
+// order: rank | digit << 16 per row; wc counts the wave's rows per digit. Rows
+// from lrem on (r * 64 >= lrem) are not counted.
+template <typename K, int ITEMS, int B>
+__device__ __forceinline__ void line_rank(const DigitFn &dig, const K (&key)[ITEMS], uint32_t lrem, uint16_t *wc,
+                                          uint32_t (&pos)[ITEMS]) {
+    if (dig.mode == kDigitHash) {
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) pos[r] = (uint32_t)(digit_source<K>(key[r], kDigitHash) >> dig.shift) & dig.mask;
+    } else {
+        using U = std::make_unsigned_t<K>;
+        const U flip = dig.mode == kDigitOrdered ? U(1) << (8 * sizeof(K) - 1) : U(0);
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) pos[r] = (uint32_t)(((U)key[r] ^ flip) >> dig.shift) & dig.mask;
+    }
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t d = pos[r];
+        const bool valid = (uint32_t)(r * kWave) < lrem;
+        const uint64_t peers = match_digit<B>(d) & __ballot(valid);
+        const uint32_t rk = rank_below(peers);
+        const uint32_t b = wc[d];
+        if (valid && rk == 0) wc[d] = (uint16_t)(b + (uint32_t)__popcll(peers));
+        pos[r] = (b + rk) | d << 16;
+        // rows one after another: their lane masks together would not fit the registers
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+template <typename T, int ITEMS>
+__device__ __forceinline__ void line_load(const T *__restrict__ in, uint32_t tile0, uint32_t nt, T (&v)[ITEMS]) {
+    constexpr uint32_t TILE = 1024u * ITEMS;
+    const uint32_t lbase = (uint32_t)((threadIdx.x / kWave) * kWave * ITEMS + lane_id());
+    const T *__restrict__ p = in + (tile0 + lbase);
+    if (nt == TILE) {
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) v[r] = p[r * kWave];
+    } else {
+        const uint32_t rem = nt > lbase ? nt - lbase : 0u;
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) v[r] = (uint32_t)(r * kWave) < rem ? p[r * kWave] : T(0);
+    }
+}
+
+// A column's values of one tile, 4 or 8 bytes wide, in one raw register array.
+template <int ITEMS, bool WIDE>
+__device__ __forceinline__ void line_load_col(const PassArgs &a, int c, uint32_t tile0, uint32_t nt,
+                                              uint32_t (&v)[WIDE ? 2 * ITEMS : ITEMS]) {
+    if (c == a.rowid_col) {
+        const uint32_t lbase = (uint32_t)((threadIdx.x / kWave) * kWave * ITEMS + lane_id());
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) v[r] = tile0 + lbase + r * kWave;
+        return;
+    }
+    if (!WIDE || c < a.n4) {
+        uint32_t x[ITEMS];
+        line_load<uint32_t, ITEMS>(static_cast<const uint32_t *>(a.col_in[c]), tile0, nt, x);
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) v[r] = x[r];
+    } else if constexpr (WIDE) {
+        uint64_t x[ITEMS];
+        line_load<uint64_t, ITEMS>(static_cast<const uint64_t *>(a.col_in[c]), tile0, nt, x);
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            v[r] = (uint32_t)x[r];
+            v[ITEMS + r] = (uint32_t)(x[r] >> 32);
+        }
+    }
+}
+
+// What one tile's columns share: the stage or carry place of each row (two to a
+// register), the output row of each of this thread's runs of four staged values,
+// and where its carry slots move.
+template <int ITEMS, int NS, int NV>
+struct LineMap {
+    uint32_t pp[ITEMS / 2];
+    uint32_t dst[NV];   // 0xFFFFFFFF: past the tile's lines
+    uint32_t part;      // bit k: run k starts before the chunk's first row of its digit
+    uint16_t move[NS];  // stage place of carry slot k * 1024 + tid, or 0xFFFF
+};
+
+// One column's staged lines to global memory, four values a thread and step.
+template <typename T, int ITEMS, int NS, int NV, int A>
+__device__ __forceinline__ void line_flush(const LineLds &S, const LineMap<ITEMS, NS, NV> &m, T *__restrict__ out) {
+    const T *stage = reinterpret_cast<const T *>(S.stage);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const uint32_t row = m.dst[k];
+        if (row == 0xFFFFFFFFu) continue;
+        const uint32_t e = (uint32_t)(k * 1024 + threadIdx.x) * 4;
+        T x[4];
+        load_run16<T, 4>(stage + e, x);
+        if ((m.part >> k) & 1u) {
+            const uint32_t first = S.pos[S.tab[e / A]].z;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (row + i >= first) out[row + i] = x[i];
+        } else {
+            store_run16<T, 4>(out + row, x);
+        }
+    }
+}
+
+// Stages one column: the carried values, then the tile's. Places from cbase on
+// are the carry's, coff places further in this column.
+template <typename T, int ITEMS, int NS, int NV, typename F>
+__device__ __forceinline__ void line_stage(const LineLds &S, const LineMap<ITEMS, NS, NV> &m, uint32_t cbase,
+                                           uint32_t coff, const T (&old)[NS], F value) {
+    T *stage = reinterpret_cast<T *>(S.stage);
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
+        if (m.move[k] != 0xFFFFu) stage[m.move[k]] = old[k];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        uint32_t p = (m.pp[r >> 1] >> (16 * (r & 1))) & 0xFFFFu;
+        if (p >= cbase) p += coff;
+        stage[p] = value(r);
+    }
+}
+
+// The values in this thread's carry slots of a column.
+template <typename T, int NS>
+__device__ __forceinline__ void line_old(const T *carry, uint32_t slots, T (&old)[NS]) {
+#pragma unroll
+    for (int k = 0; k < NS; ++k) old[k] = carry[min((uint32_t)(k * 1024 + threadIdx.x), slots - 1)];
+}
+
+// ITEMS rows per thread and tile, lines of A rows; WIDE: the key or some column
+// has 8 bytes; NS carry slots per thread (D * A <= 1024 * NS).
+template <typename K, int ITEMS, int A, bool WIDE, int NS>
+__device__ __forceinline__ void scatter_tile_lines(const PassArgs &a, const DigitFn &dig, const LineLds &S, uint32_t D,
+                                                   uint32_t tile0, uint32_t nt, K (&key)[ITEMS],
+                                                   uint32_t (&v)[WIDE ? 2 * ITEMS : ITEMS], uint32_t next0,
+                                                   uint32_t next_nt) {
+    constexpr uint32_t TILE = 1024u * ITEMS;
+    constexpr int NV = (int)((TILE + 1024u * NS + 4095) / 4096);  // runs of four values per thread
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // nothing derived from it is hoisted out of the tile loop
+    const int w = tid / kWave, lane = tid % kWave;
+    const uint32_t lbase = (uint32_t)(w * kWave * ITEMS + lane);
+    const uint32_t lrem = nt > lbase ? nt - lbase : 0u;
+    const uint32_t cbase = line_max(D, A, TILE) * A;  // places of the lines; the carry's follow
+    constexpr uint32_t SW = WIDE ? 8 : 4;
+    uint32_t *words = reinterpret_cast<uint32_t *>(S.wcnt);
+    for (uint32_t i = tid; i < kLineWaves * D / 2; i += 1024) words[i] = 0;
+    const uint8_t *carry = S.stage + (size_t)cbase * SW;
+    __syncthreads();
+    uint32_t pos[ITEMS];
+    uint16_t *wc = S.wcnt + (uint32_t)w * D;
+    line_rank<K, ITEMS, A == 32 && NS == 4 ? 7 : 8>(dig, key, lrem, wc, pos);
+    __syncthreads();
+    // per digit: rows and full lines of this tile, and the lines' exclusive prefix
+    uint32_t lines = 0, pre = 0;
+    uint4 q = make_uint4(0, 0, 0, 0);
+    if ((uint32_t)tid < kRadix) {
+        if ((uint32_t)tid < D) {
+            uint32_t t = 0;
+#pragma unroll
+            for (int x = 0; x < kLineWaves; ++x) {
+                const uint32_t c = S.wcnt[x * D + tid];
+                S.wcnt[x * D + tid] = (uint16_t)t;
+                t += c;
+            }
+            q = S.pos[tid];
+            q.x = q.y;
+            q.y += t;
+            lines = q.y / A - q.x / A;
+        }
+        const uint32_t inc = wave_inclusive_sum<uint32_t>(lines);
+        if (lane == kWave - 1) S.tmp[w] = inc;
+        pre = inc - lines;
+    }
+    __syncthreads();
+    if ((uint32_t)tid < D) {
+#pragma unroll
+        for (int x = 0; x < kRadix / kWave; ++x) pre += (x < w) ? S.tmp[x] : 0u;
+        q.w = q.x / A * A - pre * A;
+        S.pos[tid] = q;
+        S.info[tid] = (pre * A + q.x % A) | (pre + lines) * A << 16;
+        S.lbase[tid] = (uint16_t)pre;
+        if ((uint32_t)tid == D - 1) S.lbase[D] = (uint16_t)(pre + lines);
+    }
+    K kold[NS];
+    line_old<K, NS>(reinterpret_cast<const K *>(carry), D * A, kold);
+    __syncthreads();
+    LineMap<ITEMS, NS, NV> m;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t d = pos[r] >> 16;
+        const uint32_t f = S.info[d], end = f >> 16;
+        uint32_t p = (f & 0xFFFFu) + wc[d] + (pos[r] & 0xFFFFu);
+        if (p >= end) p = cbase + d * A + (p - end);
+        if ((uint32_t)(r * kWave) >= lrem) p = cbase - 1;  // no row: a place past the lines
+        if (r & 1) m.pp[r >> 1] |= p << 16;
+        else m.pp[r >> 1] = p;
+    }
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        const uint32_t s = (uint32_t)(k * 1024 + tid), d = s / A;
+        m.move[k] = 0xFFFFu;
+        if (d < D) {
+            const uint32_t l = S.lbase[d];
+            if (s % A < S.pos[d].x % A && S.lbase[d + 1] > l) m.move[k] = (uint16_t)(l * A + s % A);
+        }
+    }
+    // the places of this thread's runs: the line's digit by binary search, the run's output row from it
+    const uint32_t nl = S.lbase[D];
+    for (uint32_t l = tid; l < nl; l += 1024) {
+        uint32_t lo = 0, hi = D;  // lbase[lo] <= l < lbase[hi]
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (S.lbase[mid] <= l) lo = mid;
+            else hi = mid;
+        }
+        S.tab[l] = (uint8_t)lo;
+    }
+    // Place p of the carry of a T column lies at LDS byte cbase * SW + coff + (p - cbase) * sizeof(T).
+    line_stage<K, ITEMS, NS, NV>(S, m, cbase, cbase * SW / (uint32_t)sizeof(K) - cbase, kold,
+                                 [&](int r) { return key[r]; });
+    if (next_nt) line_load<K, ITEMS>(static_cast<const K *>(a.key_in), next0, next_nt, key);
+    __syncthreads();
+    m.part = 0;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const uint32_t e = (uint32_t)(k * 1024 + tid) * 4;
+        m.dst[k] = 0xFFFFFFFFu;
+        if (e < nl * A) {
+            const uint4 f = S.pos[S.tab[e / A]];
+            const uint32_t row = f.w + e;
+            if (row < f.z) m.part |= 1u << k;
+            if (row + 3 < a.n_rows) m.dst[k] = row;  // always true when the offsets are right
+        }
+    }
+    line_flush<K, ITEMS, NS, NV, A>(S, m, static_cast<K *>(a.key_out));
+    uint32_t coff = D * A * (uint32_t)sizeof(K);  // bytes of the carry before the column's
+#pragma unroll 1
+    for (int c = 0; c < a.ncols; ++c) {
+        const bool more = c + 1 < a.ncols;
+        // once v is staged: the next column of this tile, or the next tile's first one
+        const auto load_next = [&]() {
+            if (more || next_nt)
+                line_load_col<ITEMS, WIDE>(a, more ? c + 1 : 0, more ? tile0 : next0, more ? nt : next_nt, v);
+        };
+        // the carried values leave the carry before this tile's replace them
+        if (!WIDE || c < a.n4) {
+            uint32_t old[NS];
+            line_old<uint32_t, NS>(reinterpret_cast<const uint32_t *>(carry + coff), D * A, old);
+            __syncthreads();
+            line_stage<uint32_t, ITEMS, NS, NV>(S, m, cbase, (cbase * SW + coff) / 4 - cbase, old,
+                                                [&](int r) { return v[r]; });
+            load_next();
+            __syncthreads();
+            line_flush<uint32_t, ITEMS, NS, NV, A>(S, m, static_cast<uint32_t *>(a.col_out[c]));
+            coff += D * A * 4;
+        } else if constexpr (WIDE) {
+            uint64_t old[NS];
+            line_old<uint64_t, NS>(reinterpret_cast<const uint64_t *>(carry + coff), D * A, old);
+            __syncthreads();
+            line_stage<uint64_t, ITEMS, NS, NV>(S, m, cbase, (cbase * SW + coff) / 8 - cbase, old,
+                                                [&](int r) { return (uint64_t)v[ITEMS + r] << 32 | v[r]; });
+            load_next();
+            __syncthreads();
+            line_flush<uint64_t, ITEMS, NS, NV, A>(S, m, static_cast<uint64_t *>(a.col_out[c]));
+            coff += D * A * 8;
+        }
+    }
+    __syncthreads();  // the next tile stages its keys, and the ranks' counters restart
+}
+
+// The rows left in the carry at the end of a chunk.
+template <typename T, int A>
+__device__ __forceinline__ void line_rest(const LineLds &S, uint32_t D, const T *carry, T *__restrict__ out,
+                                          uint32_t n_rows) {
+    uint32_t s = threadIdx.x;
+    asm volatile("" : "+v"(s));  // not hoisted out of the loop over chunks
+    for (; s < D * A; s += 1024) {
+        const uint4 q = S.pos[s / A];
+        const uint32_t row = q.y / A * A + s % A;
+        if (row < q.y && row >= q.z && row < n_rows) out[row] = carry[s];
+    }
+}
+
+// One chunk: its tiles, then what is left in the carry.
+template <typename K, int ITEMS, int A, bool WIDE, int NS>
+__device__ __forceinline__ void scatter_chunk_lines(const PassArgs &a, const ChunkLoc &L, const LineLds &S, uint32_t D) {
+    constexpr uint32_t TILE = 1024u * ITEMS;
+    constexpr uint32_t SW = WIDE ? 8 : 4;
+    const uint32_t base_off = uni(a.seg_off[0]);
+    for (uint32_t d = threadIdx.x; d < D; d += 1024) {
+        const uint32_t first = base_off + a.hist[L.hbase + d * L.m + L.j];
+        S.pos[d] = make_uint4(first, first, first, 0);
+    }
+    const DigitFn dig = seg_digit(a, L.seg);
+    K key[ITEMS];
+    uint32_t v[WIDE ? 2 * ITEMS : ITEMS];
+    uint32_t tile0 = L.row0;
+    uint32_t nt = min(TILE, L.row1 - tile0);
+    line_load<K, ITEMS>(static_cast<const K *>(a.key_in), tile0, nt, key);
+    if (a.ncols > 0) line_load_col<ITEMS, WIDE>(a, 0, tile0, nt, v);
+    while (nt) {
+        const uint32_t next0 = tile0 + nt;
+        const uint32_t next_nt = next0 < L.row1 ? min(TILE, L.row1 - next0) : 0u;
+        scatter_tile_lines<K, ITEMS, A, WIDE, NS>(a, dig, S, D, tile0, nt, key, v, next0, next_nt);
+        tile0 = next0;
+        nt = next_nt;
+    }
+    const uint8_t *carry = S.stage + (size_t)line_max(D, A, TILE) * A * SW;
+    line_rest<K, A>(S, D, reinterpret_cast<const K *>(carry), static_cast<K *>(a.key_out), a.n_rows);
+    carry += (size_t)D * A * sizeof(K);
+    for (int c = 0; c < a.ncols; ++c) {
+        if (c < a.n4) {
+            line_rest<uint32_t, A>(S, D, reinterpret_cast<const uint32_t *>(carry), static_cast<uint32_t *>(a.col_out[c]), a.n_rows);
+            carry += (size_t)D * A * 4;
+        } else {
+            line_rest<uint64_t, A>(S, D, reinterpret_cast<const uint64_t *>(carry), static_cast<uint64_t *>(a.col_out[c]), a.n_rows);
+            carry += (size_t)D * A * 8;
+        }
+    }
+}
+
+template <typename K, int ITEMS, int A, bool WIDE, int NS>
+__global__ __launch_bounds__(1024) void k_scatter_lines(PassArgs a) {
+    extern __shared__ uint4 s_dyn4[];
+    const uint32_t D = 1u << a.bits;
+    const LineLds S = line_lds(reinterpret_cast<uint8_t *>(s_dyn4), D, A, a.row_bytes, 1024u * ITEMS, WIDE ? 8 : 4);
+    const uint32_t end = uni(a.seg_off[0]) + min((blockIdx.x + 1) * a.chunk_rows, a.n_rows);
+    for (uint32_t seg = cell_first_seg(a, blockIdx.x); seg < a.nseg && uni(a.seg_off[seg]) < end; ++seg) {
+        const ChunkLoc L = cell_chunk(a, blockIdx.x, seg);
+        if (L.row0 >= L.row1) continue;
+        scatter_chunk_lines<K, ITEMS, A, WIDE, NS>(a, L, S, D);
+        __syncthreads();
+    }
+}
+
 // MINW: minimum waves per SIMD the register allocation must allow (4 lets two
 // 512-thread workgroups share a compute unit).
 template <typename K, int BLOCK, int ITEMS, int G, int MINW>
@@ -655,6 +1120,36 @@ Shape scatter_shape() {
     return sh;
 }
 
+// The whole-line kernel's launch for a pass, if its LDS holds the carry and its
+// 16-byte stores may go to every output column: lines of 32 rows (128 bytes of a
+// 4-byte column) before lines of 16, long tiles before short ones.
+template <typename K>
+bool launch_lines(dim3 grid, hipStream_t s, PassArgs &a, double bytes) {
+    constexpr size_t kLds = 160 * 1024 - 128;
+    const uint32_t D = 1u << a.bits;
+    const bool wide = sizeof(K) == 8 || a.n4 < a.ncols;
+    uintptr_t at = (uintptr_t)a.key_out;
+    for (int c = 0; c < a.ncols; ++c) at |= (uintptr_t)a.col_out[c];
+    if (at & 15u) return false;
+#define GJ_LN(I, A_, W, NS)                                                                                       \
+    do {                                                                                                          \
+        const size_t lds = line_lds_bytes(D, A_, a.row_bytes, 1024u * I, W ? 8 : 4);                              \
+        if (wide == W && (size_t)D * A_ <= 1024u * NS && lds <= kLds) {                                           \
+            GJ_LAUNCH("k_scatter", bytes, (k_scatter_lines<K, I, A_, W, NS>), grid, dim3(1024), lds, s, a);       \
+            return true;                                                                                          \
+        }                                                                                                         \
+    } while (0)
+    if constexpr (sizeof(K) == 4) {
+        GJ_LN(14, 32, false, 4);
+        GJ_LN(14, 16, false, 4);
+        GJ_LN(8, 16, false, 4);
+    }
+    GJ_LN(8, 32, true, 4);
+    GJ_LN(8, 16, true, 4);
+#undef GJ_LN
+    return false;
+}
+
 template <typename K>
 void launch_scatter(const Shape &sh, dim3 grid, hipStream_t s, const PassArgs &a, double bytes) {
 #define GJ_SC(B, I, G_)                                                                    \
@@ -667,7 +1162,7 @@ void launch_scatter(const Shape &sh, dim3 grid, hipStream_t s, const PassArgs &a
     GJ_SC(256, 16, 2) GJ_SC(512, 8, 2) GJ_SC(512, 16, 2) GJ_SC(512, 16, 4) GJ_SC(1024, 8, 2)
     GJ_SC(1024, 16, 2) GJ_SC(1024, 16, 1) GJ_SC(512, 16, 1)
 #undef GJ_SC
-    if (sh.block == 1024 && sh.items == 16 && sh.group == 0) {
+    if (sh.block == 1024 && sh.items == 16 && sh.group <= 0) {
         GJ_LAUNCH("k_scatter", bytes, (k_scatter_wide<K, 1024, 16>), grid, dim3(1024), 0, s, a);
         return;
     }
@@ -732,8 +1227,24 @@ __global__ void k_key_bits(const K *__restrict__ keys, uint32_t n, unsigned long
     }
 }
 
-// Aim for ~4096 chunks: a few per resident workgroup, each a whole number of tiles.
-uint32_t chunk_rows_for(uint32_t n) {
+// Whether a pass takes long chunks and the whole-line kernel: once its output
+// outgrows the 256 MB memory-side cache, which until then puts split lines
+// together again. 4-byte data, 20 bytes a row, 7 bits: 2^24 rows 184 -> 165 us,
+// 2^26 rows 761 -> 575, 2^27 rows 1.58 -> 1.12 ms; 5 bits, whose longer runs
+// split fewer lines: 155 -> 170, 591 -> 558 us; 8 bytes a row, 2^24 rows: no gain.
+// With 8-byte keys or columns a tile has half the rows, so its fixed work weighs
+// more: 24 bytes a row, 7 bits, 2^26 rows 852 -> 817 us, 2^27 rows 1.79 -> 1.60 ms.
+// Not with many segments (a batch's instances, mostly shorter than such a chunk).
+bool long_chunks(uint32_t n, uint32_t nseg, uint32_t row_bytes, bool narrow) {
+    if (scatter_shape().group >= 0 || nseg > kRadix) return false;
+    return (uint64_t)n * row_bytes >= (narrow ? 1ull << 29 : 1ull << 31);
+}
+
+// Rows per chunk: long ones, one for each of the 256 compute units (chunks share
+// lines at their ends: 2^27 rows, 7 bits: 1.12 ms with 256 chunks, 1.20 with
+// 1024); else one tile, at most ~4096 chunks.
+uint32_t chunk_rows_for(uint32_t n, bool cells) {
+    if (cells) return ceil_div_u32(ceil_div_u32(n, 256), 1024) * 1024;
     const Shape sh = scatter_shape();
     const uint32_t tile = (uint32_t)(sh.block * sh.items);
     const uint32_t tiles = ceil_div_u32(n, tile);
@@ -746,8 +1257,13 @@ void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const uint32_t *hist8 = nullptr
     hipStream_t s = ctx.stream;
     const uint32_t R = 1u << a.bits;
     const Shape sh = scatter_shape();
-    a.chunk_rows = chunk_rows_for(n);
-    const uint64_t max_chunks = (uint64_t)ceil_div_u32(n, a.chunk_rows) + a.nseg;
+    a.row_bytes = (uint32_t)sizeof(K);
+    for (int c = 0; c < a.ncols; ++c) a.row_bytes += (uint32_t)a.col_w[c];
+    const bool narrow = sizeof(K) == 4 && a.n4 == a.ncols;
+    a.cells = long_chunks(n, a.nseg, a.row_bytes, narrow) ? 1 : 0;
+    a.chunk_rows = chunk_rows_for(n, a.cells);
+    const uint32_t cells = ceil_div_u32(n, a.chunk_rows);
+    const uint64_t max_chunks = (uint64_t)cells + a.nseg;
     uint32_t *chunk_base = ctx.scratch_n<uint32_t>(a.nseg + 1);
     a.chunk_base = chunk_base;
     const uint64_t hn = max_chunks * R;
@@ -758,7 +1274,7 @@ void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const uint32_t *hist8 = nullptr
     double row_bytes = 2.0 * sizeof(K);
     for (int c = 0; c < a.ncols; ++c) row_bytes += (c == a.rowid_col ? 0 : a.col_w[c]) + a.col_w[c];
     GJ_LAUNCH("k_chunk_table", 8.0 * (a.nseg + 1), k_chunk_table, dim3(1), dim3(kBlock), 0, s, a.seg_off,
-              a.nseg, a.chunk_rows, chunk_base);
+              a.nseg, a.chunk_rows, a.cells, chunk_base);
     fill_u32(s, hist, 0u, hn);
     if (hist8) {
         // one segment: chunks 0..m-1, the digit the low bits of the same source
@@ -767,9 +1283,13 @@ void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const uint32_t *hist8 = nullptr
                   dim3(std::min<uint32_t>(ceil_div_u32(R * m, kBlock), 4096)), dim3(kBlock), 0, s, hist8, m, a.bits,
                   hist);
     } else {
-        GJ_LAUNCH("k_hist", (double)n * sizeof(K), k_hist<K>, dim3((uint32_t)max_chunks), dim3(kBlock), 0, s, a);
+        if (a.cells)
+            GJ_LAUNCH("k_hist", (double)n * sizeof(K), k_hist_cells<K>, dim3(cells), dim3(1024), 0, s, a);
+        else
+            GJ_LAUNCH("k_hist", (double)n * sizeof(K), k_hist<K>, dim3((uint32_t)max_chunks), dim3(kBlock), 0, s, a);
     }
     scan_exclusive_u32(ctx, hist, hist, hn, nullptr);
+    if (a.cells && launch_lines<K>(dim3(cells), s, a, (double)n * row_bytes)) return;
     launch_scatter<K>(sh, dim3((uint32_t)max_chunks), s, a, (double)n * row_bytes);
 }
 
@@ -777,7 +1297,9 @@ void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const uint32_t *hist8 = nullptr
 
 void set_scatter_variant(int v) { g_variant = v; }
 
-uint32_t pass_chunk_rows(uint32_t n) { return chunk_rows_for(n); }
+uint32_t pass_chunk_rows(uint32_t n, uint32_t row_bytes, bool narrow) {
+    return chunk_rows_for(n, long_chunks(n, 1, row_bytes, narrow));
+}
 
 void partition_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, const PartCols &cols,
                    uint32_t n, int bit_lo, int bits, int passes, int mode, uint32_t *poff, const uint32_t *hist8) {
