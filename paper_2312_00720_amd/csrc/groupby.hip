@@ -706,18 +706,17 @@ __global__ __launch_bounds__(BLOCK) void k_hll(const K *__restrict__ keys, uint3
             hll_keys<K, HIST, B, U / 2>(k, valid, s_reg, cnt, o, x);
         }
     }
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-        o |= __shfl_xor(o, d, kWave);
-        x &= __shfl_xor(x, d, kWave);
-    }
-    if (lane_id() == 0) {
-        // 4-byte keys leave the upper word alone (set in the AND, clear in the OR)
-        atomicOr(&bits[0], (unsigned long long)o);
-        atomicAnd(&bits[1], (unsigned long long)x | (sizeof(K) == 4 ? 0xFFFFFFFF00000000ull : 0ull));
-    }
+    // 4-byte keys leave the upper word alone (set in the AND, clear in the OR)
+    __shared__ unsigned long long s_bits[2 * (BLOCK / kWave)];
+    fold_key_bits<BLOCK / kWave>((unsigned long long)o,
+                                 (unsigned long long)x | (sizeof(K) == 4 ? 0xFFFFFFFF00000000ull : 0ull), s_bits, bits);
     __syncthreads();
+    // Every workgroup folds into the same 1024 registers: it reads them first and
+    // raises only those it can (a value read late is only lower). Unconditional
+    // atomics of 4096 workgroups on one address each took longer than the read
+    // of the keys: 2^26 keys, 1000 groups: 395 -> 58 us (with 256 workgroups of 1024 threads).
     for (int i = threadIdx.x; i < (1 << kHllBits); i += BLOCK)
-        if (s_reg[i]) atomicMax(&regs[i], s_reg[i]);
+        if (s_reg[i] > __hip_atomic_load(&regs[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&regs[i], s_reg[i]);
     if constexpr (HIST) {
         for (int d = threadIdx.x; d < 256; d += BLOCK) {
             uint32_t t = 0;

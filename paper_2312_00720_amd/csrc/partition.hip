@@ -1197,7 +1197,7 @@ void assign_cols(PassArgs &a, const PartCols &cols, const void *const *cin, void
 }
 
 template <typename K>
-__global__ void k_key_bits(const K *__restrict__ keys, uint32_t n, unsigned long long *__restrict__ acc) {
+__global__ __launch_bounds__(256) void k_key_bits(const K *__restrict__ keys, uint32_t n, unsigned long long *__restrict__ acc) {
     // OR and AND of the order-preserving key bits over all keys, 16 loads in
     // flight per thread
     constexpr int U = 16;
@@ -1217,14 +1217,8 @@ __global__ void k_key_bits(const K *__restrict__ keys, uint32_t n, unsigned long
             x &= v;
         }
     }
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-        o |= __shfl_xor(o, d, kWave);
-        x &= __shfl_xor(x, d, kWave);
-    }
-    if (lane_id() == 0) {
-        atomicOr(&acc[0], o);
-        atomicAnd(&acc[1], x);
-    }
+    __shared__ unsigned long long s_bits[2 * (256 / kWave)];
+    fold_key_bits<256 / kWave>(o, x, s_bits, acc);
 }
 
 // Whether a pass takes long chunks and the whole-line kernel: once its output
