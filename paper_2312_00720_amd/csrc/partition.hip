@@ -5,16 +5,19 @@
 // One pass reorders rows stably by a digit of at most 8 bits. A pass works on
 // segments (pass 1: the whole input; pass 2: every partition of pass 1), which
 // are cut into chunks of whole tiles:
-//   k_chunk_table  chunks per segment and their exclusive prefix
-//   k_hist         per chunk, rows per digit -> hist[seg][digit][chunk]
+//   k_chunk_table  chunks per segment and their exclusive prefix (several
+//                  segments only)
+//   k_hist         per chunk, rows per digit -> hist[seg][digit][chunk] (not for
+//                  an input of one tile)
 //   scan           flat exclusive scan of hist = absolute output offset of each
 //                  (segment, digit, chunk) run, because that order is the
-//                  output order
+//                  output order (small passes: each scatter workgroup sums the
+//                  counts before its own)
 //   k_scatter      per chunk, tile by tile: wave-level ranking by ballot (no
 //                  atomics, so equal digits keep input order), LDS staging in
 //                  digit order, then runs written contiguously; the key and
-//                  every payload column reuse the same positions
-//   k_poff         partition boundaries (segment, digit) for the next pass
+//                  every payload column reuse the same positions. A segment's
+//                  first chunk also writes its partition boundaries
 // Two passes with the top bits first give rows sorted stably by the full digit,
 // i.e. every partition contiguous and in input order.
 #include <stdio.h>
@@ -35,6 +38,10 @@ constexpr int kItems = 16;
 constexpr int kGroup = -1;
 constexpr uint32_t kTile = kBlock * kItems;
 
+// Where a chunk's output offsets come from: the scanned counts (hist), the raw
+// counts of its segment, or the tile itself (the input is one tile).
+enum OffsetMode : int { kOffScanned = 0, kOffDirect = 1, kOffSelf = 2 };
+
 struct PassArgs {
     const void *key_in;
     void *key_out;
@@ -46,9 +53,12 @@ struct PassArgs {
     int col_w[kMaxCols];
     DigitFn dig;
     int bits;
-    const uint32_t *seg_off;  // nseg + 1 row offsets
+    const uint32_t *seg_off;  // nseg + 1 row offsets (nullptr: one segment, the whole input)
     uint32_t nseg;
-    const uint32_t *chunk_base;  // nseg + 1 chunk offsets
+    const uint32_t *chunk_base;  // nseg + 1 chunk offsets (nullptr: one segment)
+    uint32_t n_chunks;           // ceil(n_rows / chunk_rows): the chunks of a single segment
+    uint32_t *poff;              // optional: receives the partition boundaries (segment, digit)
+    int off_mode;                // OffsetMode
     uint32_t chunk_rows;
     int cells;  // long chunks (below): cut at multiples of chunk_rows of the whole input
     uint32_t *hist;  // [chunks][2^bits], laid out as (segment, digit, chunk)
@@ -56,6 +66,11 @@ struct PassArgs {
     const uint8_t *seg_bits;  // optional: digit bits per segment (<= bits; batches of instances)
     uint32_t row_bytes;       // k_scatter_lines: bytes of the key and every column
 };
+
+__device__ __forceinline__ uint32_t seg_begin(const PassArgs &a, uint32_t s) { return a.seg_off ? a.seg_off[s] : 0u; }
+__device__ __forceinline__ uint32_t seg_end(const PassArgs &a, uint32_t s) {
+    return a.seg_off ? a.seg_off[s + 1] : a.n_rows;
+}
 
 // The digit function of the segment a chunk belongs to.
 __device__ __forceinline__ DigitFn seg_digit(const PassArgs &a, uint32_t seg) {
@@ -87,11 +102,11 @@ __device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_re
 // Segment `seg` of cell `cell`: its chunk there.
 __device__ __forceinline__ ChunkLoc cell_chunk(const PassArgs &a, uint32_t cell, uint32_t seg) {
     ChunkLoc L{};
-    const uint32_t base = uni(a.seg_off[0]), s0 = uni(a.seg_off[seg]), s1 = uni(a.seg_off[seg + 1]);
-    const uint32_t cb = uni(a.chunk_base[seg]), c0 = base + cell * a.chunk_rows;
+    const uint32_t base = uni(seg_begin(a, 0)), s0 = uni(seg_begin(a, seg)), s1 = uni(seg_end(a, seg));
+    const uint32_t cb = a.chunk_base ? uni(a.chunk_base[seg]) : 0u, c0 = base + cell * a.chunk_rows;
     L.seg = seg;
     L.j = cell - (s0 - base) / a.chunk_rows;
-    L.m = uni(a.chunk_base[seg + 1]) - cb;
+    L.m = a.chunk_base ? uni(a.chunk_base[seg + 1]) - cb : a.n_chunks;
     L.row0 = max(s0, c0);
     L.row1 = min(s1, c0 + a.chunk_rows);
     L.hbase = cb << a.bits;
@@ -100,6 +115,7 @@ __device__ __forceinline__ ChunkLoc cell_chunk(const PassArgs &a, uint32_t cell,
 }
 // First segment with rows at or past the cell's first row.
 __device__ uint32_t cell_first_seg(const PassArgs &a, uint32_t cell) {
+    if (!a.seg_off) return 0u;
     const uint32_t row = a.seg_off[0] + cell * a.chunk_rows;
     uint32_t lo = 0, hi = a.nseg;  // seg_off[hi] > row
     while (hi - lo > 1) {
@@ -112,6 +128,14 @@ __device__ uint32_t cell_first_seg(const PassArgs &a, uint32_t cell) {
 
 __device__ ChunkLoc locate_chunk(const PassArgs &a, uint32_t c) {
     ChunkLoc L{};
+    if (!a.chunk_base) {  // one segment
+        L.ok = c < a.n_chunks;
+        L.j = c;
+        L.m = a.n_chunks;
+        L.row0 = c * a.chunk_rows;
+        L.row1 = (uint32_t)min<uint64_t>((uint64_t)L.row0 + a.chunk_rows, a.n_rows);
+        return L;
+    }
     const uint32_t total = a.chunk_base[a.nseg];
     if (c >= total) {
         L.ok = 0;
@@ -136,20 +160,26 @@ __device__ ChunkLoc locate_chunk(const PassArgs &a, uint32_t c) {
     return L;
 }
 
-__global__ __launch_bounds__(kBlock) void k_chunk_table(const uint32_t *__restrict__ seg_off,
-                                                        uint32_t nseg, uint32_t chunk_rows, int cells,
-                                                        uint32_t *__restrict__ chunk_base) {
-    __shared__ uint32_t s_tmp[kWaves];
+// Also writes the partition boundaries of empty segments, which no chunk visits.
+__global__ __launch_bounds__(1024) void k_chunk_table(const uint32_t *__restrict__ seg_off, uint32_t nseg,
+                                                      uint32_t chunk_rows, int cells, int bits,
+                                                      uint32_t *__restrict__ chunk_base, uint32_t *__restrict__ poff) {
+    __shared__ uint32_t s_tmp[1024 / kWave];
     uint32_t carry = 0;
-    for (uint32_t base = 0; base < nseg; base += kBlock) {
+    for (uint32_t base = 0; base < nseg; base += 1024) {
         const uint32_t s = base + threadIdx.x;
         const uint32_t cnt = s < nseg ? seg_chunks(seg_off[s], seg_off[s + 1], seg_off[0], chunk_rows, cells) : 0u;
         uint32_t tot;
-        const uint32_t ex = block_exclusive_sum<uint32_t>(cnt, s_tmp, &tot);
+        const uint32_t ex = block_exclusive_sum<uint32_t, 1024 / kWave>(cnt, s_tmp, &tot);
         if (s < nseg) chunk_base[s] = carry + ex;
+        if (s < nseg && cnt == 0 && poff)
+            for (uint32_t d = 0; d < 1u << bits; ++d) poff[((uint64_t)s << bits) + d] = seg_off[s];
         carry += tot;
     }
-    if (threadIdx.x == 0) chunk_base[nseg] = carry;
+    if (threadIdx.x == 0) {
+        chunk_base[nseg] = carry;
+        if (poff) poff[(uint64_t)nseg << bits] = seg_off[nseg];
+    }
 }
 
 // Counts of one chunk's rows per digit.
@@ -199,8 +229,8 @@ __global__ __launch_bounds__(kBlock) void k_hist(PassArgs a) {
 template <typename K>
 __global__ __launch_bounds__(1024) void k_hist_cells(PassArgs a) {
     __shared__ uint32_t s_cnt[1024 / kWave][kRadix];
-    const uint32_t end = uni(a.seg_off[0]) + min((blockIdx.x + 1) * a.chunk_rows, a.n_rows);
-    for (uint32_t seg = cell_first_seg(a, blockIdx.x); seg < a.nseg && uni(a.seg_off[seg]) < end; ++seg) {
+    const uint32_t end = uni(seg_begin(a, 0)) + min((blockIdx.x + 1) * a.chunk_rows, a.n_rows);
+    for (uint32_t seg = cell_first_seg(a, blockIdx.x); seg < a.nseg && uni(seg_begin(a, seg)) < end; ++seg) {
         const ChunkLoc L = cell_chunk(a, blockIdx.x, seg);
         if (L.row0 >= L.row1) continue;
         hist_chunk<K, 1024>(a, L, s_cnt);
@@ -221,6 +251,63 @@ __global__ void k_fold_hist(const uint32_t *__restrict__ hist8, uint32_t m, int 
         for (uint32_t q = 0; q < per; ++q) t += h[d + (q << bits)];
         hist[idx] = t;  // (segment 0, digit d, chunk j)
     }
+}
+
+// Partition boundaries of a chunk that is its segment's first (cur: its offsets).
+__device__ __forceinline__ void write_poff(const PassArgs &a, const ChunkLoc &L, const uint32_t *cur, int threads) {
+    if (!a.poff || L.j != 0) return;
+    const uint32_t R = 1u << a.bits;
+    for (uint32_t d = threadIdx.x; d < R; d += threads) a.poff[(L.seg << a.bits) + d] = cur[d];
+    if (!a.seg_off && threadIdx.x == 0) a.poff[R] = a.n_rows;  // several segments: k_chunk_table
+}
+
+// Offsets of a chunk from the raw counts of its segment: the rows of smaller
+// digits, and of its digit in earlier chunks. 16 lanes sum a digit's chunks.
+// s_tmp: 4 words.
+template <int BLOCK>
+__device__ __forceinline__ void direct_offsets(const PassArgs &a, const ChunkLoc &L, uint32_t *cur, uint32_t *s_tot,
+                                               uint32_t *s_tmp) {
+    const uint32_t R = 1u << a.bits;
+    const uint32_t *__restrict__ h = a.hist + L.hbase;
+    const uint32_t i = threadIdx.x % 16;
+    for (uint32_t d = threadIdx.x / 16; d < R; d += BLOCK / 16) {
+        uint32_t tot = 0, before = 0;
+        for (uint32_t j = i; j < L.m; j += 64) {
+            uint32_t c[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c[u] = j + u * 16 < L.m ? h[d * L.m + j + u * 16] : 0u;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                tot += c[u];
+                if (j + u * 16 < L.j) before += c[u];
+            }
+        }
+#pragma unroll
+        for (int k = 8; k > 0; k >>= 1) {
+            tot += __shfl_xor(tot, k, 16);
+            before += __shfl_xor(before, k, 16);
+        }
+        if (i == 0) {
+            s_tot[d] = tot;
+            cur[d] = before;
+        }
+    }
+    __syncthreads();
+    const int t = threadIdx.x, w = t / kWave;
+    uint32_t inc = 0, x = 0;
+    if (t < kRadix) {
+        x = (uint32_t)t < R ? s_tot[t] : 0u;
+        inc = wave_inclusive_sum<uint32_t>(x);
+        if (lane_id() == kWave - 1) s_tmp[w] = inc;
+    }
+    __syncthreads();
+    if (t < kRadix && (uint32_t)t < R) {
+        uint32_t pre = seg_begin(a, L.seg) + inc - x;
+#pragma unroll
+        for (int q = 0; q < kRadix / kWave; ++q) pre += q < w ? s_tmp[q] : 0u;
+        cur[t] += pre;
+    }
+    __syncthreads();
 }
 
 // Loads of one tile: ITEMS keys per thread and the first group of up to G 4-byte
@@ -265,8 +352,8 @@ struct ScatterShared {
 };
 
 template <typename K, int BLOCK, int ITEMS, int G>
-__device__ __forceinline__ void scatter_tile(const PassArgs &a, const DigitFn &dig, ScatterShared<BLOCK> &S,
-                                             uint32_t (*s_buf)[BLOCK * ITEMS], uint32_t tile0, uint32_t nt,
+__device__ __forceinline__ void scatter_tile(const PassArgs &a, const ChunkLoc &L, const DigitFn &dig,
+                                             ScatterShared<BLOCK> &S, uint32_t (*s_buf)[BLOCK * ITEMS], uint32_t tile0, uint32_t nt,
                                              K (&key)[ITEMS], uint32_t next0, uint32_t next_nt) {
     constexpr int W = BLOCK / kWave;
     const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
@@ -324,8 +411,10 @@ __device__ __forceinline__ void scatter_tile(const PassArgs &a, const DigitFn &d
 #pragma unroll
         for (int q = 0; q < kWaves; ++q) before += (q < w) ? S.tmp[q] : 0u;
         S.start[tid] += before;
+        if (a.off_mode == kOffSelf) S.cur[tid] = S.start[tid];  // the only tile
     }
     __syncthreads();
+    if (a.off_mode == kOffSelf) write_poff(a, L, S.cur, BLOCK);
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         if (GJ_VALID(r)) {
@@ -616,9 +705,11 @@ __global__ __launch_bounds__(BLOCK) void k_scatter_wide(PassArgs a) {
     if (!L.ok) return;
 
     const uint32_t R = 1u << a.bits;
-    const uint32_t base_off = a.seg_off[0];
+    const uint32_t base_off = seg_begin(a, 0);
     for (uint32_t d = threadIdx.x; d < kRadix; d += BLOCK)
         S.cur[d] = d < R ? base_off + a.hist[L.hbase + d * L.m + L.j] : 0u;
+    __syncthreads();
+    write_poff(a, L, S.cur, BLOCK);
 
     const DigitFn dig = seg_digit(a, L.seg);
     K key[ITEMS];
@@ -993,11 +1084,13 @@ template <typename K, int ITEMS, int A, bool WIDE, int NS>
 __device__ __forceinline__ void scatter_chunk_lines(const PassArgs &a, const ChunkLoc &L, const LineLds &S, uint32_t D) {
     constexpr uint32_t TILE = 1024u * ITEMS;
     constexpr uint32_t SW = WIDE ? 8 : 4;
-    const uint32_t base_off = uni(a.seg_off[0]);
+    const uint32_t base_off = uni(seg_begin(a, 0));
     for (uint32_t d = threadIdx.x; d < D; d += 1024) {
         const uint32_t first = base_off + a.hist[L.hbase + d * L.m + L.j];
         S.pos[d] = make_uint4(first, first, first, 0);
+        if (a.poff && L.j == 0) a.poff[(L.seg << a.bits) + d] = first;
     }
+    if (a.poff && L.j == 0 && !a.seg_off && threadIdx.x == 0) a.poff[D] = a.n_rows;
     const DigitFn dig = seg_digit(a, L.seg);
     K key[ITEMS];
     uint32_t v[WIDE ? 2 * ITEMS : ITEMS];
@@ -1031,8 +1124,8 @@ __global__ __launch_bounds__(1024) void k_scatter_lines(PassArgs a) {
     extern __shared__ uint4 s_dyn4[];
     const uint32_t D = 1u << a.bits;
     const LineLds S = line_lds(reinterpret_cast<uint8_t *>(s_dyn4), D, A, a.row_bytes, 1024u * ITEMS, WIDE ? 8 : 4);
-    const uint32_t end = uni(a.seg_off[0]) + min((blockIdx.x + 1) * a.chunk_rows, a.n_rows);
-    for (uint32_t seg = cell_first_seg(a, blockIdx.x); seg < a.nseg && uni(a.seg_off[seg]) < end; ++seg) {
+    const uint32_t end = uni(seg_begin(a, 0)) + min((blockIdx.x + 1) * a.chunk_rows, a.n_rows);
+    for (uint32_t seg = cell_first_seg(a, blockIdx.x); seg < a.nseg && uni(seg_begin(a, seg)) < end; ++seg) {
         const ChunkLoc L = cell_chunk(a, blockIdx.x, seg);
         if (L.row0 >= L.row1) continue;
         scatter_chunk_lines<K, ITEMS, A, WIDE, NS>(a, L, S, D);
@@ -1055,9 +1148,15 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_scatter(PassArgs a) {
     if (!L.ok) return;
 
     const uint32_t R = 1u << a.bits;
-    const uint32_t base_off = a.seg_off[0];
-    for (uint32_t d = threadIdx.x; d < kRadix; d += BLOCK)
-        S.cur[d] = d < R ? base_off + a.hist[L.hbase + d * L.m + L.j] : 0u;
+    if (a.off_mode == kOffDirect) {
+        direct_offsets<BLOCK>(a, L, S.cur, S.tot, S.tmp);
+    } else if (a.off_mode == kOffScanned) {
+        const uint32_t base_off = seg_begin(a, 0);
+        for (uint32_t d = threadIdx.x; d < kRadix; d += BLOCK)
+            S.cur[d] = d < R ? base_off + a.hist[L.hbase + d * L.m + L.j] : 0u;
+        __syncthreads();
+    }
+    if (a.off_mode != kOffSelf) write_poff(a, L, S.cur, BLOCK);
 
     const DigitFn dig = seg_digit(a, L.seg);
     K key[ITEMS];
@@ -1067,31 +1166,9 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_scatter(PassArgs a) {
     while (nt) {
         const uint32_t next0 = tile0 + nt;
         const uint32_t next_nt = next0 < L.row1 ? min(TILE, L.row1 - next0) : 0u;
-        scatter_tile<K, BLOCK, ITEMS, G>(a, dig, S, s_buf, tile0, nt, key, next0, next_nt);
+        scatter_tile<K, BLOCK, ITEMS, G>(a, L, dig, S, s_buf, tile0, nt, key, next0, next_nt);
         tile0 = next0;
         nt = next_nt;
-    }
-}
-
-__global__ void k_poff(const uint32_t *__restrict__ seg_off, uint32_t nseg,
-                       const uint32_t *__restrict__ chunk_base, const uint32_t *__restrict__ hist,
-                       int bits, uint32_t *__restrict__ poff) {
-    const uint32_t R = 1u << bits;
-    const uint64_t total = (uint64_t)nseg * R;
-    const uint32_t base_off = seg_off[0];
-    for (uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t s = (uint32_t)(idx >> bits), d = (uint32_t)(idx & (R - 1));
-        const uint32_t cb = chunk_base[s], m = chunk_base[s + 1] - cb;
-        poff[idx] = m ? base_off + hist[((uint64_t)cb << bits) + (uint64_t)d * m] : seg_off[s];
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) poff[total] = seg_off[nseg];
-}
-
-__global__ void k_set_range(uint32_t *p, uint32_t a, uint32_t b) {
-    if (threadIdx.x == 0) {
-        p[0] = a;
-        p[1] = b;
     }
 }
 
@@ -1117,6 +1194,20 @@ Shape scatter_shape() {
         }
         return x;
     }();
+    return sh;
+}
+
+// The shape of a pass over n rows in nseg segments. Where no shape was asked
+// for, tiles shrink with the input so that they still fill the chip: scatter of
+// key + column by 5 bits, 2^18 rows: 18.3 us in 16384-row tiles, 9.1 in
+// 2048-row ones; 2^20 rows: 19.7 and 11.7 us; 2^22 rows 33 us, 30 in 4096-row
+// tiles (with four columns 46 and 42); 2^23 rows with four columns: 85 and 89 us.
+Shape pass_shape(uint32_t n, uint32_t nseg) {
+    const Shape sh = scatter_shape();
+    if (sh.group >= 0) return sh;
+    const uint32_t avg = n / (nseg > kRadix ? nseg : 1);  // a batch's tiles end with its instances
+    if (n <= 1u << 20 || avg <= 4096) return Shape{512, 4, 4};
+    if (n <= 3u << 21 || avg <= 16384) return Shape{512, 8, 4};
     return sh;
 }
 
@@ -1237,53 +1328,66 @@ bool long_chunks(uint32_t n, uint32_t nseg, uint32_t row_bytes, bool narrow) {
 // Rows per chunk: long ones, one for each of the 256 compute units (chunks share
 // lines at their ends: 2^27 rows, 7 bits: 1.12 ms with 256 chunks, 1.20 with
 // 1024); else one tile, at most ~4096 chunks.
-uint32_t chunk_rows_for(uint32_t n, bool cells) {
+uint32_t chunk_rows_for(uint32_t n, uint32_t nseg, bool cells) {
     if (cells) return ceil_div_u32(ceil_div_u32(n, 256), 1024) * 1024;
-    const Shape sh = scatter_shape();
+    const Shape sh = pass_shape(n, nseg);
     const uint32_t tile = (uint32_t)(sh.block * sh.items);
     const uint32_t tiles = ceil_div_u32(n, tile);
     const uint32_t per = tiles > 4096 ? ceil_div_u32(tiles, 4096) : 1;
     return per * tile;
 }
 
+// Counts a chunk's workgroup may sum itself instead of a scan (kOffDirect): 64 KB
+// of them from L2 take about a microsecond, a scan's launch about five.
+constexpr uint64_t kDirectCounts = 16384;
+
 template <typename K>
 void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const uint32_t *hist8 = nullptr) {
     hipStream_t s = ctx.stream;
     const uint32_t R = 1u << a.bits;
-    const Shape sh = scatter_shape();
     a.row_bytes = (uint32_t)sizeof(K);
     for (int c = 0; c < a.ncols; ++c) a.row_bytes += (uint32_t)a.col_w[c];
     const bool narrow = sizeof(K) == 4 && a.n4 == a.ncols;
     a.cells = long_chunks(n, a.nseg, a.row_bytes, narrow) ? 1 : 0;
-    a.chunk_rows = chunk_rows_for(n, a.cells);
-    const uint32_t cells = ceil_div_u32(n, a.chunk_rows);
-    const uint64_t max_chunks = (uint64_t)cells + a.nseg;
-    uint32_t *chunk_base = ctx.scratch_n<uint32_t>(a.nseg + 1);
-    a.chunk_base = chunk_base;
-    const uint64_t hn = max_chunks * R;
-    uint32_t *hist = ctx.scratch_n<uint32_t>(hn);
-    a.hist = hist;
+    a.chunk_rows = chunk_rows_for(n, a.nseg, a.cells);
+    a.n_chunks = ceil_div_u32(n, a.chunk_rows);
+    const Shape sh = pass_shape(n, a.nseg);
+    const uint64_t max_chunks = a.seg_off ? (uint64_t)a.n_chunks + a.nseg : a.n_chunks;
     // algorithmic bytes of one scatter: read and write the key and every column
     // once (a generated row id is only written)
     double row_bytes = 2.0 * sizeof(K);
     for (int c = 0; c < a.ncols; ++c) row_bytes += (c == a.rowid_col ? 0 : a.col_w[c]) + a.col_w[c];
-    GJ_LAUNCH("k_chunk_table", 8.0 * (a.nseg + 1), k_chunk_table, dim3(1), dim3(kBlock), 0, s, a.seg_off,
-              a.nseg, a.chunk_rows, a.cells, chunk_base);
-    fill_u32(s, hist, 0u, hn);
+    const bool tiled = !a.cells && sh.group > 0;  // k_scatter: it can find its offsets itself
+    if (tiled && !a.seg_off && a.n_chunks == 1) {
+        a.off_mode = kOffSelf;
+        launch_scatter<K>(sh, dim3(1), s, a, (double)n * row_bytes);
+        return;
+    }
+    if (a.seg_off) {
+        uint32_t *chunk_base = ctx.scratch_n<uint32_t>(a.nseg + 1);
+        a.chunk_base = chunk_base;
+        GJ_LAUNCH("k_chunk_table", 8.0 * (a.nseg + 1), k_chunk_table, dim3(1), dim3(1024), 0, s, a.seg_off, a.nseg,
+                  a.chunk_rows, a.cells, a.bits, chunk_base, a.poff);
+    }
+    // counts past the chunks in use stay unwritten: a scan carries them to no one
+    const uint64_t hn = max_chunks * R;
+    uint32_t *hist = ctx.scratch_n<uint32_t>(hn);
+    a.hist = hist;
     if (hist8) {
         // one segment: chunks 0..m-1, the digit the low bits of the same source
-        const uint32_t m = ceil_div_u32(n, a.chunk_rows);
+        const uint32_t m = a.n_chunks;
         GJ_LAUNCH("k_fold_hist", 4.0 * m * 256 + 4.0 * m * R, k_fold_hist,
                   dim3(std::min<uint32_t>(ceil_div_u32(R * m, kBlock), 4096)), dim3(kBlock), 0, s, hist8, m, a.bits,
                   hist);
     } else {
         if (a.cells)
-            GJ_LAUNCH("k_hist", (double)n * sizeof(K), k_hist_cells<K>, dim3(cells), dim3(1024), 0, s, a);
+            GJ_LAUNCH("k_hist", (double)n * sizeof(K), k_hist_cells<K>, dim3(a.n_chunks), dim3(1024), 0, s, a);
         else
             GJ_LAUNCH("k_hist", (double)n * sizeof(K), k_hist<K>, dim3((uint32_t)max_chunks), dim3(kBlock), 0, s, a);
     }
-    scan_exclusive_u32(ctx, hist, hist, hn, nullptr);
-    if (a.cells && launch_lines<K>(dim3(cells), s, a, (double)n * row_bytes)) return;
+    if (tiled && hn <= kDirectCounts) a.off_mode = kOffDirect;
+    else scan_exclusive_u32(ctx, hist, hist, hn, nullptr);
+    if (a.cells && launch_lines<K>(dim3(a.n_chunks), s, a, (double)n * row_bytes)) return;
     launch_scatter<K>(sh, dim3((uint32_t)max_chunks), s, a, (double)n * row_bytes);
 }
 
@@ -1292,7 +1396,7 @@ void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const uint32_t *hist8 = nullptr
 void set_scatter_variant(int v) { g_variant = v; }
 
 uint32_t pass_chunk_rows(uint32_t n, uint32_t row_bytes, bool narrow) {
-    return chunk_rows_for(n, long_chunks(n, 1, row_bytes, narrow));
+    return chunk_rows_for(n, 1, long_chunks(n, 1, row_bytes, narrow));
 }
 
 void partition_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, const PartCols &cols,
@@ -1317,9 +1421,12 @@ void partition_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, c
     for (int c = 0; c < cols.n; ++c) cin[c] = cols.in[c];
     if (cols.gen_rowid) cin[cols.n] = nullptr;
 
+    if (n == 0) {
+        fill_u32(s, poff, 0u, (1ull << bits) + 1);
+        return;
+    }
     int map[kMaxCols];
-    uint32_t *seg = ctx.scratch_n<uint32_t>(2);
-    GJ_LAUNCH("k_set_range", 8.0, k_set_range, dim3(1), dim3(64), 0, s, seg, 0u, n);
+    const uint32_t *seg = nullptr;  // pass 1: the whole input
     uint32_t nseg = 1;
 
     for (int p = 0; p < passes; ++p) {
@@ -1340,19 +1447,11 @@ void partition_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, c
         a.seg_off = seg;
         a.nseg = nseg;
         a.n_rows = n;
-        if (n > 0) {
-            if (key_bytes == 4) run_pass<int32_t>(ctx, a, n, hist8);
-            else run_pass<int64_t>(ctx, a, n, hist8);
-        } else {
-            uint32_t *cb = ctx.scratch_n<uint32_t>(nseg + 1);
-            fill_u32(s, cb, 0u, nseg + 1);
-            a.chunk_base = cb;
-            a.hist = ctx.scratch_n<uint32_t>(1);
-        }
         const uint64_t np = (uint64_t)nseg << b[p];
         uint32_t *next = last ? poff : ctx.scratch_n<uint32_t>(np + 1);
-        GJ_LAUNCH("k_poff", 8.0 * (np + 1), k_poff, dim3((uint32_t)std::min<uint64_t>((np + 255) / 256, 4096)),
-                  dim3(256), 0, s, seg, nseg, a.chunk_base, a.hist, b[p], next);
+        a.poff = next;
+        if (key_bytes == 4) run_pass<int32_t>(ctx, a, n, hist8);
+        else run_pass<int64_t>(ctx, a, n, hist8);
         seg = next;
         nseg = (uint32_t)np;
         kin = a.key_out;
@@ -1386,8 +1485,6 @@ void sort_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, const 
             if ((diff >> (8 * b)) & 0xFF) passes.push_back(b);
     }
     if (passes.empty()) passes.push_back(0);  // a pass on an equal digit is a stable copy
-    uint32_t *seg = ctx.scratch_n<uint32_t>(2);
-    GJ_LAUNCH("k_set_range", 8.0, k_set_range, dim3(1), dim3(64), 0, s, seg, 0u, n);
     const void *kin = key_in;
     const void *cin[kMaxCols];
     for (int c = 0; c < cols.n; ++c) cin[c] = cols.in[c];
@@ -1419,7 +1516,6 @@ void sort_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, const 
         assign_cols(a, cols, cin, cout, p == 0, map);
         a.bits = 8;
         a.dig = DigitFn{kDigitOrdered, 8 * passes[p], 0xFFu};
-        a.seg_off = seg;
         a.nseg = 1;
         a.n_rows = n;
         if (n > 0) {
@@ -1457,18 +1553,10 @@ void partition_run_segments(Ctx &ctx, int key_bytes, const void *key_in, void *k
     a.nseg = nseg;
     a.n_rows = n;
     a.seg_bits = seg_bits;
-    if (n > 0) {
-        if (key_bytes == 4) run_pass<int32_t>(ctx, a, n);
-        else run_pass<int64_t>(ctx, a, n);
-    } else {
-        uint32_t *cb = ctx.scratch_n<uint32_t>(nseg + 1);
-        fill_u32(s, cb, 0u, nseg + 1);
-        a.chunk_base = cb;
-        a.hist = ctx.scratch_n<uint32_t>(1);
-    }
-    const uint64_t np = (uint64_t)nseg << 8;
-    GJ_LAUNCH("k_poff", 8.0 * (np + 1), k_poff, dim3((uint32_t)std::min<uint64_t>((np + 255) / 256, 4096)),
-              dim3(256), 0, s, seg_off, nseg, a.chunk_base, a.hist, 8, poff);
+    a.poff = poff;
+    if (n == 0) fill_u32(s, poff, 0u, ((uint64_t)nseg << 8) + 1);  // every segment is empty at row 0
+    else if (key_bytes == 4) run_pass<int32_t>(ctx, a, n);
+    else run_pass<int64_t>(ctx, a, n);
 }
 
 }  // namespace gj

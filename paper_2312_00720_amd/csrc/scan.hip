@@ -1,5 +1,6 @@
-// Device-wide exclusive prefix sums (reduce, scan of block totals, downsweep)
-// and fill kernels. The scans give the stable scatter offsets and partition
+// Device-wide exclusive prefix sums (one workgroup; or reduce and downsweep, whose
+// workgroups add up the block totals before them; or reduce, scan of block totals,
+// downsweep) and fill kernels. The scans give the stable scatter offsets and partition
 // boundaries of the radix partition (Section 4.1.4: a histogram plus a prefix
 // sum locate every partition) and the output offsets of the join and group-by.
 // Deterministic: no atomics decide any order.
@@ -10,6 +11,11 @@ namespace {
 
 constexpr int kItems = 16;
 constexpr uint32_t kTile = kBlock * kItems;
+// Up to kOneBlock values one workgroup scans in the time of a launch (about 5 us);
+// up to kSumBlocks tiles the downsweep adds the totals itself (8 KB from L2)
+// instead of a third launch.
+constexpr uint64_t kOneBlock = 32768;
+constexpr uint64_t kSumBlocks = 2048;
 
 // Element count: nmax, or min(nmax, *n_dev * mult) when the count lives in device
 // memory (launches sized for nmax; blocks past the count do nothing).
@@ -66,13 +72,25 @@ __global__ __launch_bounds__(kBlock) void k_scan_partials(T *__restrict__ partia
     if (threadIdx.x == 0 && total_out) *total_out = carry;
 }
 
-template <typename T>
+// SUM: partial holds the raw block totals; every workgroup adds up those before it
+// (at most kSumBlocks), and the last one writes the grand total.
+template <typename T, bool SUM>
 __global__ __launch_bounds__(kBlock) void k_scan_down(const T *in, T *out, uint64_t nmax,
                                                       const uint32_t *n_dev, uint32_t mult,
-                                                      const T *__restrict__ partial) {
+                                                      const T *__restrict__ partial, T *__restrict__ total_out) {
     __shared__ T s_tmp[kWaves];
     const uint64_t n = scan_len(nmax, n_dev, mult);
-    if ((uint64_t)blockIdx.x * kTile >= n) return;
+    if ((uint64_t)blockIdx.x * kTile >= n) {
+        if (SUM && n == 0 && blockIdx.x == 0 && threadIdx.x == 0 && total_out) *total_out = 0;
+        return;
+    }
+    T before = 0;
+    if constexpr (SUM) {
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kBlock) before += partial[i];
+        block_exclusive_sum<T>(before, s_tmp, &before);
+    } else {
+        before = partial[blockIdx.x];
+    }
     const uint64_t first = (uint64_t)blockIdx.x * kTile + (uint64_t)threadIdx.x * kItems;
     // a whole run of this thread's items at 16-byte aligned addresses moves in
     // 16-byte accesses
@@ -90,7 +108,9 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const T *in, T *out, uint6
     }
 #pragma unroll
     for (int k = 0; k < kItems; ++k) sum += v[k];
-    T run = partial[blockIdx.x] + block_exclusive_sum<T>(sum, s_tmp, (T *)nullptr);
+    T all;
+    T run = before + block_exclusive_sum<T>(sum, s_tmp, &all);
+    if (SUM && total_out && threadIdx.x == 0 && (uint64_t)(blockIdx.x + 1) * kTile >= n) *total_out = before + all;
     if (vec) {
         T o[kItems];
 #pragma unroll
@@ -107,6 +127,48 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const T *in, T *out, uint6
             run += v[k];
         }
     }
+}
+
+// One workgroup scans everything, a tile at a time.
+template <typename T>
+__global__ __launch_bounds__(1024) void k_scan_one(const T *in, T *out, uint64_t nmax, const uint32_t *n_dev,
+                                                   uint32_t mult, T *__restrict__ total_out) {
+    constexpr int IT = 16;
+    __shared__ T s_tmp[1024 / kWave];
+    const uint64_t n = scan_len(nmax, n_dev, mult);
+    const bool vec = (((uintptr_t)in | (uintptr_t)out) & 15u) == 0;
+    T carry = 0;
+    for (uint64_t base = 0; base < n; base += 1024 * IT) {
+        const uint64_t first = base + (uint64_t)threadIdx.x * IT;
+        const bool whole = vec && first + IT <= n;
+        T v[IT];
+        T sum = 0;
+        if (whole) {
+            load_run16<T>(in + first, v);
+        } else {
+#pragma unroll
+            for (int k = 0; k < IT; ++k) v[k] = first + k < n ? in[first + k] : T(0);
+        }
+#pragma unroll
+        for (int k = 0; k < IT; ++k) sum += v[k];
+        T all;
+        T run = carry + block_exclusive_sum<T, 1024 / kWave>(sum, s_tmp, &all);
+        carry += all;
+#pragma unroll
+        for (int k = 0; k < IT; ++k) {
+            const T x = v[k];
+            v[k] = run;
+            run += x;
+        }
+        if (whole) {
+            store_run16<T>(out + first, v);
+        } else {
+#pragma unroll
+            for (int k = 0; k < IT; ++k)
+                if (first + k < n) out[first + k] = v[k];
+        }
+    }
+    if (threadIdx.x == 0 && total_out) *total_out = carry;
 }
 
 template <typename T>
@@ -127,14 +189,23 @@ void scan_exclusive(Ctx &ctx, const T *in, T *out, uint64_t n, T *total, const u
         return;
     }
     const uint64_t blocks = (n + kTile - 1) / kTile;
-    T *partial = ctx.scratch_n<T>(blocks);
     const double nb = (double)n * sizeof(T);
+    if (n <= kOneBlock) {
+        GJ_LAUNCH("k_scan_one", 2.0 * nb, k_scan_one<T>, dim3(1), dim3(1024), 0, s, in, out, n, n_dev, mult, total);
+        return;
+    }
+    T *partial = ctx.scratch_n<T>(blocks);
     GJ_LAUNCH("k_scan_reduce", nb, k_scan_reduce<T>, dim3((uint32_t)blocks), dim3(kBlock), 0, s, in, n, n_dev,
               mult, partial);
+    if (blocks <= kSumBlocks) {
+        GJ_LAUNCH("k_scan_down", 2.0 * nb, (k_scan_down<T, true>), dim3((uint32_t)blocks), dim3(kBlock), 0, s, in, out,
+                  n, n_dev, mult, (const T *)partial, total);
+        return;
+    }
     GJ_LAUNCH("k_scan_partials", 2.0 * blocks * sizeof(T), k_scan_partials<T>, dim3(1), dim3(kBlock), 0, s,
               partial, blocks, n_dev, mult, total);
-    GJ_LAUNCH("k_scan_down", 2.0 * nb, k_scan_down<T>, dim3((uint32_t)blocks), dim3(kBlock), 0, s, in, out,
-              n, n_dev, mult, (const T *)partial);
+    GJ_LAUNCH("k_scan_down", 2.0 * nb, (k_scan_down<T, false>), dim3((uint32_t)blocks), dim3(kBlock), 0, s, in, out,
+              n, n_dev, mult, (const T *)partial, (T *)nullptr);
 }
 
 template <typename T>

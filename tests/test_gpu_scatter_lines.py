@@ -104,3 +104,32 @@ def test_large_pass_into_unaligned_outputs(shift):
     for a, b, x in zip(out, [key, *cols], room):
         assert torch.equal(a, b[perm])
         assert bool((x[:shift] == -9).all()) and bool((x[shift + n:] == -9).all())
+
+
+PASS_CASES = [
+    # n, bits, passes: one tile (no histogram), counts summed by the scatter, scanned by
+    # one workgroup and by several; the shapes' and the second pass's boundaries
+    (1, 8, 1), (2047, 3, 1), (2048, 8, 1), (2049, 8, 1),
+    (131072, 8, 1), (131073, 8, 1), (300001, 5, 1), (1 << 20, 5, 1), ((1 << 20) + 1, 8, 1),
+    ((3 << 21), 4, 1), ((3 << 21) + 1, 8, 1),
+    (2049, 16, 2), (40000, 9, 2), (1 << 20, 12, 2), (1500001, 10, 2),
+]
+
+
+@pytest.mark.parametrize("n,bits,passes", PASS_CASES)
+@pytest.mark.parametrize("kb,kind", [(32, "any"), (64, "skew")])
+def test_pass_shapes_match_stable_sort(n, bits, passes, kb, kind):
+    import torch
+    import paper_2312_00720_amd as gj
+    print(f"pass n={n} bits={bits} passes={passes} kb={kb} {kind}", flush=True)
+    key = _keys(n, torch.int32 if kb == 32 else torch.int64, kind, seed=n + bits)
+    if kind == "skew":
+        key = key & 0x0F0F0F0F0F0F0F0F  # most segments of a second pass are empty
+    cols = [torch.arange(n, device="cuda", dtype=torch.int32) * 3, torch.arange(n, device="cuda", dtype=torch.int64) - 7]
+    k, c, r, off = gj.partition(key, cols, bits=bits, passes=passes, rowid=True)
+    d = _digit(key, 0, bits, "bits")
+    perm = torch.sort(d, stable=True).indices
+    count = torch.bincount(d, minlength=1 << bits)
+    assert torch.equal(off, torch.cat([count.new_zeros(1), torch.cumsum(count, 0)]).to(torch.int32))
+    assert torch.equal(k, key[perm]) and torch.equal(r, perm.to(torch.int32))
+    assert torch.equal(c[0], cols[0][perm]) and torch.equal(c[1], cols[1][perm])
