@@ -365,8 +365,7 @@ int gj_join_batch(const gj_rel_batch *R, const gj_rel_batch *S, const gj_join_op
         const int64_t T = gj::join_partitioned(ctx, kb, side[0], side[1], 0, r_block, gfur, &jo, d_bits, (uint32_t)n,
                                                inst_off);
         std::vector<uint64_t> h(n + 1);
-        GJ_HIP(hipMemcpyAsync(h.data(), inst_off, 8ull * (n + 1), hipMemcpyDeviceToHost, st));
-        GJ_HIP(hipStreamSynchronize(st));
+        gj::read_back_parts(st, {{h.data(), inst_off, 8ull * (n + 1)}});
         for (int i = 0; i <= n; ++i) out_offsets[i] = (int64_t)h[i];
         out->n_rows = T;
         if (T > 0) {

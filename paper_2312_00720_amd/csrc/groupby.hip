@@ -2250,20 +2250,18 @@ double estimate_groups(Ctx &ctx, int key_bytes, const void *key, uint32_t n, int
             GJ_LAUNCH("k_hll", 8.0 * n, (k_hll<int64_t, false, kBlock>), dim3(grid), dim3(kBlock), 0, st,
                       static_cast<const int64_t *>(key), n, regs, bits, 0u, nullptr);
     }
-    std::vector<uint32_t> h(m + 4);
-    GJ_HIP(hipMemcpyAsync(h.data(), regs, 4ull * (m + 4), hipMemcpyDeviceToHost, st));
-    GJ_HIP(hipStreamSynchronize(st));
+    uint32_t h[m + 4];
+    read_back_parts(st, {{h, regs, sizeof(h)}});
     if (varying_bytes) {
         const uint64_t o = (uint64_t)h[m] | ((uint64_t)h[m + 1] << 32), a = (uint64_t)h[m + 2] | ((uint64_t)h[m + 3] << 32);
         for (int b = 0; b < key_bytes; ++b) *varying_bytes += (((o ^ a) >> (8 * b)) & 0xFF) != 0;
     }
-    h.resize(m);
-    double sum = 0.0;
-    int zeros = 0;
-    for (uint32_t r : h) {
-        sum += std::ldexp(1.0, -(int)r);
-        zeros += (r == 0);
-    }
+    int rank[64] = {0};  // registers per rank
+    for (int i = 0; i < m; ++i) ++rank[std::min<uint32_t>(h[i], 63)];
+    double sum = 0.0;  // exact: at most 2^10 terms, multiples of 2^-23
+    for (int r = 0; r < 64; ++r)
+        if (rank[r]) sum += rank[r] * std::ldexp(1.0, -r);
+    const int zeros = rank[0];
     const double alpha = 0.7213 / (1.0 + 1.079 / m);
     double e = alpha * m * (double)m / sum;
     if (e <= 2.5 * m && zeros > 0) e = m * std::log((double)m / zeros);  // small-range correction
@@ -2330,10 +2328,7 @@ int64_t groupby_partition(Ctx &ctx, int key_bytes, const void *key, const ValCol
               0, st, poff, (const uint32_t *)gcnt, np, ucnt, stat + 2);
     scan_exclusive_u32(ctx, ucnt, ucnt, np, ucnt + np);
     uint32_t host[5];
-    GJ_HIP(hipMemcpyAsync(&host[0], gcnt + np, 4, hipMemcpyDeviceToHost, st));
-    GJ_HIP(hipMemcpyAsync(&host[1], stat, 12, hipMemcpyDeviceToHost, st));
-    GJ_HIP(hipMemcpyAsync(&host[4], ucnt + np, 4, hipMemcpyDeviceToHost, st));
-    GJ_HIP(hipStreamSynchronize(st));
+    read_back_parts(st, {{&host[0], gcnt + np, 4}, {&host[1], stat, 12}, {&host[4], ucnt + np, 4}});
     const uint32_t g = host[0], maxg = host[1], over = host[2], max_units = host[3], units = host[4];
     if (over) {
         *fell_back = 1;  // some partition holds more distinct keys than its LDS table
@@ -2588,8 +2583,7 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
             }
         }
         uint32_t h[2];
-        GJ_HIP(hipMemcpyAsync(h, a.ngroups, 8, hipMemcpyDeviceToHost, st));
-        GJ_HIP(hipStreamSynchronize(st));
+        read_back_parts(st, {{h, a.ngroups, 8}});
         return std::make_pair(h[0], h[1] != 0);
     };
     std::pair<uint32_t, bool> r{0, true};

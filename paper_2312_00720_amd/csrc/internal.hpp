@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -90,7 +91,21 @@ class Ctx {
         if (!committed_)
             for (void *p : outputs_) release(p);
     }
+    // Small requests share blocks of kSlab bytes: a call makes a dozen or two of
+    // them, and each request to the caller's allocator costs more than a
+    // microsecond (through the Python binding).
     void *scratch(size_t bytes) {
+        if (bytes <= kSlabMost && !arena_) {
+            const size_t need = bytes == 0 ? 256 : (bytes + 255) & ~size_t(255);
+            if (!slab_ || slab_used_ + need > kSlab) {
+                slab_ = static_cast<char *>(get(kSlab));
+                scratch_.push_back(slab_);
+                slab_used_ = 0;
+            }
+            void *p = slab_ + slab_used_;
+            slab_used_ += need;
+            return p;
+        }
         void *p = get(bytes);
         scratch_.push_back(p);
         return p;
@@ -135,16 +150,28 @@ class Ctx {
             (void)hipFreeAsync(p, stream);
         }
     }
+    static constexpr size_t kSlab = 256 * 1024, kSlabMost = 32 * 1024;
+    char *slab_ = nullptr;
+    size_t slab_used_ = 0;
     std::vector<void *> scratch_, outputs_;
     bool committed_ = false;
     Arena *arena_ = nullptr;
 };
 
+// ---- readback.hip -----------------------------------------------------------------
+// Copies whole words of device memory (at most four parts) to the host, in stream
+// order, and waits for the stream.
+struct ReadPart {
+    void *host;
+    const void *dev;
+    size_t bytes;
+};
+void read_back_parts(hipStream_t s, std::initializer_list<ReadPart> parts);
+
 template <typename T>
 inline T read_back(const T *dev, hipStream_t s) {
     T v{};
-    GJ_HIP(hipMemcpyAsync(&v, dev, sizeof(T), hipMemcpyDeviceToHost, s));
-    GJ_HIP(hipStreamSynchronize(s));
+    read_back_parts(s, {{&v, dev, sizeof(T)}});
     return v;
 }
 

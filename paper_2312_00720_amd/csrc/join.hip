@@ -983,9 +983,7 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
         grid = std::max<uint32_t>(1, std::min<uint32_t>(cap_units, kPersistentGrid));
     } else {
         uint32_t hf[6];
-        GJ_HIP(hipMemcpyAsync(&cap_units, ucnt + np, 4, hipMemcpyDeviceToHost, s));
-        GJ_HIP(hipMemcpyAsync(hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s));
-        GJ_HIP(hipStreamSynchronize(s));
+        read_back_parts(s, {{&cap_units, ucnt + np, 4}, {hf, flags, sizeof(hf)}});
         // hf[2]: most R rows in a partition that S probes (a block holds at most r_block)
         lds_rows = std::max<uint32_t>(64, (std::min<uint32_t>(hf[2], (uint32_t)r_block) + 63) & ~63u);
         if (hf[3]) throw Error(GJ_EOVERFLOW, "more than 2^31-1 join work units (R partitions far larger than the "
@@ -1043,9 +1041,7 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
         *out = pl->out;
     } else {
         uint32_t hf[3];
-        GJ_HIP(hipMemcpyAsync(&T, total, 8, hipMemcpyDeviceToHost, s));
-        GJ_HIP(hipMemcpyAsync(hf, flags, 12, hipMemcpyDeviceToHost, s));
-        GJ_HIP(hipStreamSynchronize(s));
+        read_back_parts(s, {{&T, total, 8}, {hf, flags, 12}});
         complex = (hf[0] | hf[1]) != 0;
         max_r_rows = hf[2];
     }

@@ -1478,8 +1478,7 @@ void sort_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, const 
             GJ_LAUNCH("k_key_bits", 8.0 * n, k_key_bits<int64_t>, dim3(grid), dim3(256), 0, s,
                       static_cast<const int64_t *>(key_in), n, acc);
         uint64_t h[2];
-        GJ_HIP(hipMemcpyAsync(h, acc, 16, hipMemcpyDeviceToHost, s));
-        GJ_HIP(hipStreamSynchronize(s));
+        read_back_parts(s, {{h, acc, 16}});
         const uint64_t diff = h[0] ^ h[1];
         for (int b = 0; b < key_bytes; ++b)
             if ((diff >> (8 * b)) & 0xFF) passes.push_back(b);

@@ -624,17 +624,13 @@ int gj_groupby_plan_result(gj_plan *P, void *stream, gj_groupby_out *out, int64_
     if (!P || !out) return plan_error(GJ_EINVAL, "null argument");
     if (P->kind != 1) return plan_error(GJ_EINVAL, "not a group-by plan");
     try {
-        GJ_HIP(hipStreamSynchronize((hipStream_t)stream));
         const int ng = (int)P->groups.size();
-        std::vector<uint64_t> base(ng + 1);
+        std::vector<uint64_t> base(ng + 1), off(group_offsets ? P->n + 1 : 0);
         std::vector<uint32_t> status(2 * ng);
-        GJ_HIP(hipMemcpy(base.data(), P->d_base, 8 * (ng + 1), hipMemcpyDeviceToHost));
-        GJ_HIP(hipMemcpy(status.data(), P->d_gstatus, 8 * ng, hipMemcpyDeviceToHost));
-        if (group_offsets) {
-            std::vector<uint64_t> off(P->n + 1);
-            GJ_HIP(hipMemcpy(off.data(), P->d_inst_off, 8 * (P->n + 1), hipMemcpyDeviceToHost));
-            for (int i = 0; i <= P->n; ++i) group_offsets[i] = (int64_t)off[i];
-        }
+        gj::read_back_parts((hipStream_t)stream, {{base.data(), P->d_base, 8ull * (ng + 1)},
+                                                  {status.data(), P->d_gstatus, 8ull * ng},
+                                                  {off.data(), P->d_inst_off, 8 * off.size()}});
+        for (size_t i = 0; i < off.size(); ++i) group_offsets[i] = (int64_t)off[i];
         out->n_groups = (int64_t)base[ng];
         out->key = P->out_key;
         if (out->aggs)
@@ -705,17 +701,13 @@ int gj_join_plan_result(gj_plan *P, void *stream, gj_join_out *out, int64_t *out
     if (P->kind != 0) return plan_error(GJ_EINVAL, "not a join plan");
     try {
         hipStream_t st = (hipStream_t)stream;
-        GJ_HIP(hipStreamSynchronize(st));
         const int ng = (int)P->groups.size();
-        std::vector<uint64_t> base(ng + 1);
+        std::vector<uint64_t> base(ng + 1), off(out_offsets ? P->n + 1 : 0);
         std::vector<uint32_t> units(ng);
-        GJ_HIP(hipMemcpy(base.data(), P->d_base, 8 * (ng + 1), hipMemcpyDeviceToHost));
-        GJ_HIP(hipMemcpy(units.data(), P->d_units, 4 * ng, hipMemcpyDeviceToHost));
-        if (out_offsets) {
-            std::vector<uint64_t> off(P->n + 1);
-            GJ_HIP(hipMemcpy(off.data(), P->d_inst_off, 8 * (P->n + 1), hipMemcpyDeviceToHost));
-            for (int i = 0; i <= P->n; ++i) out_offsets[i] = (int64_t)off[i];
-        }
+        gj::read_back_parts(st, {{base.data(), P->d_base, 8ull * (ng + 1)},
+                                 {units.data(), P->d_units, 4ull * ng},
+                                 {off.data(), P->d_inst_off, 8 * off.size()}});
+        for (size_t i = 0; i < off.size(); ++i) out_offsets[i] = (int64_t)off[i];
         const uint64_t T = base[ng];
         out->n_rows = (int64_t)T;
         out->key = P->out_key;
