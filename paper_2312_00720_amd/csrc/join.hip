@@ -95,8 +95,12 @@ struct JoinArgs {
     uint16_t *midx;
     uint32_t *flags;            // [2]: most R rows in one partition (for LDS staging)
     int lds_if_complex;         // LDS write pass: do nothing unless a flag is set (plans)
-    uint32_t rlds_off[8];       // staged streaming pass: byte offset of R column j in LDS
+    uint32_t rlds_off[8];       // staged passes: byte offset of R column j in LDS
+    int rstaged;                // LDS write pass: R columns 0..rstaged-1 have a place there
 };
+
+// LDS an eager LDS write pass may use for its table and staged R payloads.
+constexpr size_t kJoinWriteLds = 156 * 1024;
 
 // Most work units one call may have: unit indices and their scanned offsets
 // are 32-bit.
@@ -442,7 +446,129 @@ __device__ __forceinline__ void count_unit(const JoinArgs &a, uint32_t u, const 
     }
     const uint64_t tot = wave_sum<uint64_t>((uint64_t)cnt);
     if (lane == 0) a.wcnt[(uint64_t)u * kWv + w] = tot;
-    if (a.flags && __ballot(multi) && lane == 0) atomicOr(&a.flags[1], 1u);
+    // one flag for every wave of the pass: an atomic only while it is not set yet
+    // (2^24 x 2^24 rows with duplicate keys, 33 thousand waves: 396 -> 89 us)
+    if (a.flags && __ballot(multi) && lane == 0 &&
+        !__hip_atomic_load(&a.flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicOr(&a.flags[1], 1u);
+}
+
+// Columns j0..ncols-1 of U output rows per lane: src[j][row[u]] to dst[j][p + u * 64],
+// rows with u * 64 < n only. A column's loads are issued before its stores.
+template <int U>
+__device__ __forceinline__ void emit_cols(int j0, int ncols, const void *const *src, const int *width,
+                                          void *const *dst, const uint32_t (&row)[U], uint64_t p, uint32_t n) {
+    for (int j = j0; j < ncols; ++j) {
+        if (width[j] == 4) {
+            const uint32_t *__restrict__ in = static_cast<const uint32_t *>(src[j]);
+            uint32_t *__restrict__ out = static_cast<uint32_t *>(dst[j]) + p;
+            uint32_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = in[row[u]];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u * kWave < n) out[u * kWave] = v[u];
+        } else {
+            const uint64_t *__restrict__ in = static_cast<const uint64_t *>(src[j]);
+            uint64_t *__restrict__ out = static_cast<uint64_t *>(dst[j]) + p;
+            uint64_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = in[row[u]];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u * kWave < n) out[u * kWave] = v[u];
+        }
+    }
+}
+
+// Matches of S rows [ws, we) of a unit where S rows match several R rows and
+// equal keys adjoin in the table's buckets. A wave takes 64 S rows at a time, and then
+// its lanes take their output rows, 64 consecutive ones per access: lane o finds the S row
+// that owns output o by a search over the rows' exclusive match counts, and its
+// match at that distance from the row's first. (Each lane writing the matches of
+// its own S row touched eight lines an access where this touches two: 2^24 x 2^24
+// rows, four matches each, two payloads a side: 1.5-1.7 ms -> 0.95 ms, 0.80 ms with
+// the R payloads in LDS. The waves wait for S payloads and for each other between
+// build and probe; LDS and vector units are a quarter busy.)
+template <typename K>
+__device__ __forceinline__ void write_dups(const JoinArgs &a, const JoinLds<K> &sh, const uint8_t *s_pay, uint32_t r0,
+                                           uint32_t s0, uint32_t ws, uint32_t we, int skip_bits, int log2nb,
+                                           uint64_t outpos) {
+    constexpr int U = 4;
+    const int lane = lane_id();
+    const K *__restrict__ skey = static_cast<const K *>(a.skey) + s0;
+    K *__restrict__ tkey = static_cast<K *>(a.tkey);
+    K next = ws + lane < we ? skey[ws + lane] : K(0);
+    for (uint32_t base = ws; base < we; base += kWave) {
+        const K key = next;
+        const bool valid = base + lane < we;
+        if (base + kWave < we) next = base + kWave + lane < we ? skey[base + kWave + lane] : K(0);
+        uint32_t c = 0, e1 = 0;
+        if (valid) {
+            const uint32_t b = bucket_of<K>(key, skip_bits, log2nb);
+            const uint32_t hi = sh.b[b + 1];
+            e1 = sh.b[b];
+            while (e1 < hi && sh.rkey[e1] != key) ++e1;
+            uint32_t e2 = e1;
+            while (e2 < hi && sh.rkey[e2] == key) ++e2;
+            c = e2 - e1;
+        }
+        const uint32_t incl = wave_inclusive_sum<uint32_t>(c), ex = incl - c;
+        const uint32_t t = __builtin_amdgcn_readlane(incl, kWave - 1);
+        for (uint32_t o0 = 0; o0 < t; o0 += kWave * U) {
+            uint32_t rrow[U], srow[U];
+            K kv[U];
+            const uint64_t p = outpos + o0 + lane;
+            // rows of this lane: those with o0 + lane + u * 64 < t, within the output
+            uint32_t n = o0 + lane < t ? t - o0 - lane : 0u;
+            n = p < a.t_rows ? (uint32_t)min<uint64_t>(n, a.t_rows - p) : 0u;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t o = min(o0 + lane + u * kWave, t - 1);
+                int l = 0;  // the last lane with ex <= o: it has matches
+#pragma unroll
+                for (int d = kWave / 2; d > 0; d >>= 1) {
+                    const uint32_t x = __shfl(ex, l + d, kWave);
+                    if (x <= o) l += d;
+                }
+                const uint32_t e = __shfl(e1, l, kWave) + o - __shfl(ex, l, kWave);
+                kv[u] = sh.rkey[e];
+                rrow[u] = r0 + sh.entry[e];
+                srow[u] = s0 + base + l;
+            }
+            if (a.srow) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    srow[u] = (uint32_t)a.srow[srow[u]];
+                    rrow[u] = (uint32_t)a.rrow[rrow[u]];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u * kWave < n) tkey[p + u * kWave] = kv[u];
+            emit_cols<U>(0, a.ns, a.sp, a.sw, a.ts, srow, p, n);
+            for (int j = 0; j < a.rstaged; ++j) {
+                uint32_t lrow[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) lrow[u] = rrow[u] - r0;
+                if (a.rw[j] == 4) {
+                    const uint32_t *col = reinterpret_cast<const uint32_t *>(s_pay + a.rlds_off[j]);
+                    uint32_t *__restrict__ out = static_cast<uint32_t *>(a.tr[j]) + p;
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (u * kWave < n) out[u * kWave] = col[lrow[u]];
+                } else {
+                    const uint64_t *col = reinterpret_cast<const uint64_t *>(s_pay + a.rlds_off[j]);
+                    uint64_t *__restrict__ out = static_cast<uint64_t *>(a.tr[j]) + p;
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (u * kWave < n) out[u * kWave] = col[lrow[u]];
+                }
+            }
+            emit_cols<U>(a.rstaged, a.nr, a.rp, a.rw, a.tr, rrow, p, n);
+        }
+        outpos += t;
+    }
 }
 
 // Write pass of unit u on the LDS table (the general case: partitions spanning
@@ -488,7 +614,9 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
         s_entry[slot] = (uint16_t)i;
     }
     __syncthreads();
-    // chains in row order, so that every S row emits its matches in R's input order
+    // chains in row order, so that every S row emits its matches in R's input
+    // order; where S rows match several R rows, in (key, row) order
+    const bool dups = a.flags[1] != 0;
     for (uint32_t b = tid; b < nb; b += kBlockT) {
         const uint32_t lo = s_b[b], hi = s_b[b + 1];
         if (hi - lo > kMaxChainSort) {
@@ -496,8 +624,9 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
         } else {
             for (uint32_t x = lo + 1; x < hi; ++x) {
                 const uint16_t e = s_entry[x];
+                const K ek = s_rkey[e];
                 uint32_t y = x;
-                while (y > lo && s_entry[y - 1] > e) {
+                while (y > lo && (dups && s_rkey[s_entry[y - 1]] != ek ? s_rkey[s_entry[y - 1]] > ek : s_entry[y - 1] > e)) {
                     s_entry[y] = s_entry[y - 1];
                     --y;
                 }
@@ -556,7 +685,25 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
     const K *__restrict__ skey = static_cast<const K *>(a.skey);
     const uint32_t q = ceil_div_u32(sn, kWv);
     const uint32_t ws = min(sn, w * q), we = min(sn, ws + q);
-    {
+    if (dups && !s_long) {
+        // R payloads that fit beside the table: read once, in order, into LDS (each
+        // is used by several output rows, and their gathers were what the waves
+        // waited for)
+        uint8_t *s_pay = reinterpret_cast<uint8_t *>(sh.is_long) + 8;
+        for (int j = 0; j < a.rstaged; ++j) {
+            if (a.rw[j] == 4) {
+                const uint32_t *__restrict__ in = static_cast<const uint32_t *>(a.rp[j]) + r0;
+                uint32_t *d = reinterpret_cast<uint32_t *>(s_pay + a.rlds_off[j]);
+                for (uint32_t i = tid; i < rn; i += kBlockT) d[i] = in[i];
+            } else {
+                const uint64_t *__restrict__ in = static_cast<const uint64_t *>(a.rp[j]) + r0;
+                uint64_t *d = reinterpret_cast<uint64_t *>(s_pay + a.rlds_off[j]);
+                for (uint32_t i = tid; i < rn; i += kBlockT) d[i] = in[i];
+            }
+        }
+        __syncthreads();
+        write_dups<K>(a, sh, s_pay, r0, s0, ws, we, skip_bits, log2nb, out_base + a.woff[(uint64_t)u * kWv + w]);
+    } else {
         uint64_t outpos = out_base + a.woff[(uint64_t)u * kWv + w];
         K *__restrict__ tkey = static_cast<K *>(a.tkey);
         for (uint32_t base = ws; base < we; base += PB * kWave) {
@@ -916,15 +1063,27 @@ struct JoinKernels {
     static void staged(hipStream_t s, uint32_t grid, size_t shm, const JoinArgs &a, double bytes) {
         GJ_LAUNCH("k_join_write", bytes, (k_join_stream_staged<K, BUILD>), dim3(grid), dim3(G::kThreads), shm, s, a);
     }
-    static void write_lds(hipStream_t s, bool planned, uint32_t grid, const JoinArgs &a, double bytes) {
-        const size_t shm = join_lds_bytes<K, BUILD>(a.lds_rows);
+    // R payload columns beside the table, as many as fit (S rows with several matches)
+    static size_t stage_r(JoinArgs &a) {
+        size_t shm = join_lds_bytes<K, BUILD>(a.lds_rows), used = 0;
+        for (; a.rstaged < a.nr; ++a.rstaged) {
+            const size_t b = ((size_t)a.lds_rows * a.rw[a.rstaged] + 15) & ~(size_t)15;
+            if (shm + used + b > kJoinWriteLds) break;
+            a.rlds_off[a.rstaged] = (uint32_t)used;
+            used += b;
+        }
+        return shm + used;
+    }
+    static void write_lds(hipStream_t s, bool planned, uint32_t grid, JoinArgs a, double bytes, bool dups) {
+        const size_t shm = dups ? stage_r(a) : join_lds_bytes<K, BUILD>(a.lds_rows);
         if (planned) GJ_LAUNCH("k_join_write_lds", bytes, (k_join_persist<K, BUILD, true>), dim3(grid), dim3(G::kThreads), shm, s, a);
         else GJ_LAUNCH("k_join_write_lds", bytes, (k_join<K, BUILD, true>), dim3(grid), dim3(G::kThreads), shm, s, a);
     }
 };
 
 // Pass 0 = count, 1 = streaming write, 2 = LDS write, 3 = streaming write with
-// the R side staged in shm bytes of LDS; the table shape holds r_block rows.
+// the R side staged in shm bytes of LDS; the table shape holds r_block rows. Pass 2
+// with shm != 0: S rows match several R rows, R payloads may be staged.
 void launch_join_pass(int pass, int key_bytes, uint32_t table_rows, hipStream_t s, bool planned, uint32_t grid,
                       const JoinArgs &a, double bytes, size_t shm = 0) {
 #define GJ_JP(K, B)                                                 \
@@ -932,7 +1091,7 @@ void launch_join_pass(int pass, int key_bytes, uint32_t table_rows, hipStream_t 
         if (pass == 0) JoinKernels<K, B>::count(s, planned, grid, a, bytes);     \
         else if (pass == 1) JoinKernels<K, B>::stream(s, grid, a, bytes);        \
         else if (pass == 3) JoinKernels<K, B>::staged(s, grid, shm, a, bytes);   \
-        else JoinKernels<K, B>::write_lds(s, planned, grid, a, bytes);           \
+        else JoinKernels<K, B>::write_lds(s, planned, grid, a, bytes, shm != 0); \
     } while (0)
     if (key_bytes == 4) {
         if (table_rows == 4096) GJ_JP(int32_t, 4096);
@@ -1035,6 +1194,7 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
     else scan_exclusive_u64(ctx, wcnt, wcnt, nw, total);
     uint64_t T;
     bool complex = true;  // plans launch both write passes; each decides on the device
+    bool dups = false;    // eager calls: some S row matches several R rows
     uint32_t max_r_rows = 0;
     if (pl) {
         T = pl->out_cap;  // stores are checked against the capacity; the true count stays on the device
@@ -1043,6 +1203,7 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
         uint32_t hf[3];
         read_back_parts(s, {{&T, total, 8}, {hf, flags, 12}});
         complex = (hf[0] | hf[1]) != 0;
+        dups = hf[1] != 0;
         max_r_rows = hf[2];
     }
     if (inst_off)
@@ -1104,7 +1265,7 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
     else if (pl || !complex) launch_join_pass(1, key_bytes, table_rows, s, pl != nullptr, grid, a, sbytes);
     if (pl || complex) {
         const double lbytes = pl ? 0.0 : wbytes;  // a plan counts its bytes once, on the streaming pass
-        launch_join_pass(2, key_bytes, table_rows, s, pl != nullptr, grid, a, lbytes);
+        launch_join_pass(2, key_bytes, table_rows, s, pl != nullptr, grid, a, lbytes, dups && !gfur ? 1 : 0);
     }
     return pl ? 0 : (int64_t)T;
 }
