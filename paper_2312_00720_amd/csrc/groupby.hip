@@ -542,6 +542,11 @@ __global__ void k_pgb_status(const uint64_t *__restrict__ base, const uint32_t *
     }
 }
 
+// *p = max(*p, v) where many workgroups meet on one word: no atomic that would not raise it.
+__device__ __forceinline__ void raise_max(uint32_t *p, uint32_t v) {
+    if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
+}
+
 template <typename K>
 __device__ __forceinline__ K empty_key() {
     if constexpr (sizeof(K) == 4) return (K)INT32_MIN;
@@ -744,6 +749,7 @@ struct PgbArgs {
     // aggregation pass
     const uint32_t *goff;   // exclusive prefix of gcnt
     const uint32_t *ubase;  // exclusive prefix of units per partition
+    const uint32_t *umap;   // partition of every unit (k_pgb_unit_map)
     void *out_key;
     AggSpec spec;
     ValSrc vals;
@@ -764,14 +770,15 @@ template <typename K>
 __global__ __launch_bounds__(kBlock) void k_pgb_discover(PgbArgs a) {
     __shared__ K s_key[kDiscoverCap];
     __shared__ uint32_t s_first[kDiscoverCap];
-    __shared__ uint32_t s_tmp[kWaves];
     __shared__ uint32_t s_sent;  // first row holding the key equal to the empty marker
     __shared__ int s_over;
+    constexpr int HB = 16;
+    __shared__ uint32_t s_rw[HB][kWaves];
     constexpr int log2cap = 12;
     static_assert((1u << log2cap) == kDiscoverCap, "table size");
     const uint32_t p = blockIdx.x;
     const uint32_t p0 = a.poff[p], p1 = a.poff[p + 1];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, w = tid / kWave;
     if (p0 == p1) {
         if (tid == 0) a.gcnt[p] = 0;
         return;
@@ -779,6 +786,67 @@ __global__ __launch_bounds__(kBlock) void k_pgb_discover(PgbArgs a) {
     if (p1 - p0 > kDiscoverUnit) return;  // discovered by k_pgb_discover_unit + k_pgb_merge
     const K *__restrict__ keys = static_cast<const K *>(a.keys);
     const K e = empty_key<K>();
+    if (p1 - p0 <= kDiscoverCap / 2) {
+        // A partition of at most 2048 rows, eight to a thread: the keys are read once
+        // and every row keeps its slot, so the id pass neither reads nor
+        // probes again; the table has two to four slots per row.
+        constexpr int RB = kDiscoverCap / 2 / kBlock;
+        const uint32_t rows = p1 - p0;
+        K kk[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) kk[r] = r * kBlock + tid < rows ? keys[p0 + r * kBlock + tid] : e;
+        int l2 = 6;
+        while ((1u << l2) < 2 * rows) ++l2;
+        for (uint32_t i = tid; i < 1u << l2; i += kBlock) {
+            s_key[i] = e;
+            s_first[i] = 0xFFFFFFFFu;
+        }
+        if (tid == 0) s_sent = 0xFFFFFFFFu;
+        __syncthreads();
+        uint32_t slot[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const uint32_t local = r * kBlock + tid;
+            slot[r] = 0xFFFFFFFFu;
+            if (local >= rows) continue;
+            if (kk[r] == e) {
+                atomicMin(&s_sent, local);
+            } else {
+                slot[r] = (uint32_t)lds_insert<K>(s_key, l2, kk[r]);  // never full
+                if (s_first[slot[r]] > local) atomicMin(&s_first[slot[r]], local);
+            }
+        }
+        __syncthreads();
+        uint32_t hmask = 0, rk[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const uint32_t local = r * kBlock + tid;
+            const bool head = local < rows && (kk[r] == e ? s_sent == local : s_first[slot[r]] == local);
+            const uint64_t m = __ballot(head);
+            rk[r] = rank_below(m);
+            if (head) hmask |= 1u << r;
+            if (lane_id() == 0) s_rw[r][w] = (uint32_t)__popcll(m);
+        }
+        __syncthreads();
+        K *__restrict__ tk = static_cast<K *>(a.tmp_keys) + p0;
+        uint32_t tot = 0;  // heads before the round's wave 0
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            uint32_t before = tot;
+#pragma unroll
+            for (int q = 0; q < kWaves; ++q) {
+                const uint32_t c = s_rw[r][q];
+                if (q < w) before += c;
+                tot += c;
+            }
+            if (hmask & (1u << r)) tk[before + rk[r]] = kk[r];
+        }
+        if (tid == 0) {
+            a.gcnt[p] = tot;
+            raise_max(&a.stat[0], tot);
+        }
+        return;
+    }
     for (uint32_t i = tid; i < kDiscoverCap; i += kBlock) {
         s_key[i] = e;
         s_first[i] = 0xFFFFFFFFu;
@@ -823,9 +891,6 @@ __global__ __launch_bounds__(kBlock) void k_pgb_discover(PgbArgs a) {
     // Every (round, wave) counts its heads by ballot; one barrier later each thread
     // knows how many heads come before its row from those counts and its rank.
     K *__restrict__ tk = static_cast<K *>(a.tmp_keys);
-    constexpr int HB = 16;
-    __shared__ uint32_t s_rw[HB][kWaves];
-    const int w = tid / kWave;
     uint32_t ids = 0;
     for (uint32_t c0 = p0; c0 < p1; c0 += kBlock * HB) {
         K kk[HB];
@@ -869,7 +934,7 @@ __global__ __launch_bounds__(kBlock) void k_pgb_discover(PgbArgs a) {
     }
     if (tid == 0) {
         a.gcnt[p] = ids;
-        atomicMax(&a.stat[0], ids);
+        raise_max(&a.stat[0], ids);
     }
 }
 
@@ -961,10 +1026,18 @@ __global__ __launch_bounds__(kBlock) void k_pgb_merge(PgbArgs a) {
     __shared__ uint32_t s_tmp[kWaves];
     __shared__ int s_sent, s_over;
     constexpr int log2cap = 12;
-    const uint32_t p = blockIdx.x;
     const int tid = threadIdx.x;
+    // a workgroup per slice: the one of a partition's first slice merges it (a
+    // workgroup per partition spent 38 us on 2^17 empty ones)
+    if (blockIdx.x >= a.dubase[a.np]) return;
+    uint32_t p = 0;
+    for (uint32_t hi = a.np; hi - p > 1;) {  // dubase[p] <= blockIdx.x < dubase[hi]
+        const uint32_t mid = (p + hi) >> 1;
+        if (a.dubase[mid] <= blockIdx.x) p = mid;
+        else hi = mid;
+    }
     const uint32_t u0 = a.dubase[p], u1 = a.dubase[p + 1];
-    if (u0 == u1) return;  // not an oversized partition
+    if (blockIdx.x != u0) return;
     // a slice overflowed (here or in another partition): the result is discarded
     // (hash group-by takes over, or a plan reports the overflow), so nothing is
     // merged; the group count is still defined for the kernels that follow
@@ -1038,7 +1111,7 @@ __global__ __launch_bounds__(kBlock) void k_pgb_merge(PgbArgs a) {
     for (uint32_t i = tid; i < cnt; i += kBlock) tk[p0 + off + i] = s_sort[i];
     if (tid == 0) {
         a.gcnt[p] = cnt + off;
-        atomicMax(&a.stat[0], cnt + off);
+        raise_max(&a.stat[0], cnt + off);
     }
 }
 
@@ -1060,7 +1133,25 @@ __global__ void k_pgb_units(const uint32_t *__restrict__ poff, const uint32_t *_
         ucnt[p] = u;
         mx = max(mx, u);
     }
-    atomicMax(max_units, mx);
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) mx = max(mx, (uint32_t)__shfl_xor(mx, d, kWave));
+    if (lane_id() == 0) raise_max(max_units, mx);
+}
+
+// The partition of every aggregation unit, found once: a binary search by each
+// unit's workgroup was 17 dependent loads at the 2^17 partitions of a batch.
+__global__ void k_pgb_unit_map(const uint32_t *__restrict__ ubase, uint32_t np, uint32_t cap,
+                               uint32_t *__restrict__ umap) {
+    const uint32_t n = min(ubase[np], cap);
+    for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) {
+        uint32_t lo = 0, hi = np;  // ubase[lo] <= u < ubase[hi]
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (ubase[mid] <= u) lo = mid;
+            else hi = mid;
+        }
+        umap[u] = lo;
+    }
 }
 
 template <typename K, int NV, int BT, bool SKEW, typename V>
@@ -1069,13 +1160,7 @@ __device__ __forceinline__ void pgb_unit(const PgbArgs &a, uint32_t u, uint64_t 
     constexpr int RB = NV <= 2 ? 8 : 16 / NV;  // rows loaded per thread before they are aggregated
     const int tid = threadIdx.x, lane = lane_id();
     if (tid == 0) {
-        uint32_t lo = 0, hi = a.np;  // ubase[lo] <= u < ubase[hi]
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (a.ubase[mid] <= u) lo = mid;
-            else hi = mid;
-        }
-        const uint32_t p = lo;
+        const uint32_t p = a.umap[u];
         const uint32_t p0 = a.poff[p], p1 = a.poff[p + 1];
         const uint32_t j = u - a.ubase[p];
         const uint32_t ur = unit_rows_for(a.goff[p + 1] - a.goff[p]);
@@ -2268,6 +2353,14 @@ double estimate_groups(Ctx &ctx, int key_bytes, const void *key, uint32_t n, int
     return std::min(e, (double)n);
 }
 
+static const uint32_t *pgb_unit_map(Ctx &ctx, const uint32_t *ubase, uint32_t np, uint32_t cap) {
+    uint32_t *umap = ctx.scratch_n<uint32_t>(std::max<uint32_t>(cap, 1));
+    GJ_LAUNCH("k_pgb_unit_map", 4.0 * cap, k_pgb_unit_map,
+              dim3(std::max<uint32_t>(1, std::min<uint32_t>(ceil_div_u32(cap, 256), 1024))), dim3(256), 0, ctx.stream,
+              ubase, np, cap, umap);
+    return umap;
+}
+
 int64_t groupby_partition(Ctx &ctx, int key_bytes, const void *key, const ValCols &vc,
                           uint32_t n, const gj_agg *aggs, int n_aggs, bool gfur, int bits, void **out_key,
                           void **out_aggs, int *fell_back, const uint32_t *hist8) {
@@ -2316,11 +2409,11 @@ int64_t groupby_partition(Ctx &ctx, int key_bytes, const void *key, const ValCol
     if (key_bytes == 4) {
         GJ_LAUNCH("k_pgb_discover", 8.0 * n, k_pgb_discover<int32_t>, dim3(np), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_discover", 0.0, k_pgb_discover_unit<int32_t>, dim3(max_du), dim3(kBlock), 0, st, a);
-        GJ_LAUNCH("k_pgb_merge", 8.0 * np, k_pgb_merge<int32_t>, dim3(np), dim3(kBlock), 0, st, a);
+        GJ_LAUNCH("k_pgb_merge", 8.0 * np, k_pgb_merge<int32_t>, dim3(max_du), dim3(kBlock), 0, st, a);
     } else {
         GJ_LAUNCH("k_pgb_discover", 16.0 * n, k_pgb_discover<int64_t>, dim3(np), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_discover", 0.0, k_pgb_discover_unit<int64_t>, dim3(max_du), dim3(kBlock), 0, st, a);
-        GJ_LAUNCH("k_pgb_merge", 16.0 * np, k_pgb_merge<int64_t>, dim3(np), dim3(kBlock), 0, st, a);
+        GJ_LAUNCH("k_pgb_merge", 16.0 * np, k_pgb_merge<int64_t>, dim3(max_du), dim3(kBlock), 0, st, a);
     }
     scan_exclusive_u32(ctx, gcnt, gcnt, np, gcnt + np);
     uint32_t *ucnt = ctx.scratch_n<uint32_t>(np + 1);
@@ -2349,6 +2442,7 @@ int64_t groupby_partition(Ctx &ctx, int key_bytes, const void *key, const ValCol
     a.out_key = *out_key;
     a.nunits = ucnt + np;
     a.cap_units = units;
+    a.umap = pgb_unit_map(ctx, ucnt, np, units);
     a.out_base = nullptr;
     a.lds_bytes = 0;
     // LDS: the aggregation table (key and group id per slot), then maxg records and
@@ -2454,11 +2548,11 @@ void groupby_partition_segments(Ctx &ctx, int key_bytes, const void *key, const 
     if (key_bytes == 4) {
         GJ_LAUNCH("k_pgb_discover", 8.0 * n, k_pgb_discover<int32_t>, dim3(np), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_discover", 0.0, k_pgb_discover_unit<int32_t>, dim3(max_du), dim3(kBlock), 0, st, a);
-        GJ_LAUNCH("k_pgb_merge", 8.0 * np, k_pgb_merge<int32_t>, dim3(np), dim3(kBlock), 0, st, a);
+        GJ_LAUNCH("k_pgb_merge", 8.0 * np, k_pgb_merge<int32_t>, dim3(max_du), dim3(kBlock), 0, st, a);
     } else {
         GJ_LAUNCH("k_pgb_discover", 16.0 * n, k_pgb_discover<int64_t>, dim3(np), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_discover", 0.0, k_pgb_discover_unit<int64_t>, dim3(max_du), dim3(kBlock), 0, st, a);
-        GJ_LAUNCH("k_pgb_merge", 16.0 * np, k_pgb_merge<int64_t>, dim3(np), dim3(kBlock), 0, st, a);
+        GJ_LAUNCH("k_pgb_merge", 16.0 * np, k_pgb_merge<int64_t>, dim3(max_du), dim3(kBlock), 0, st, a);
     }
     scan_exclusive_u32(ctx, gcnt, gcnt, np, gcnt + np);
     uint32_t *ucnt = ctx.scratch_n<uint32_t>(np + 1);
@@ -2473,6 +2567,7 @@ void groupby_partition_segments(Ctx &ctx, int key_bytes, const void *key, const 
     a.out_key = pl.out_key;
     a.nunits = ucnt + np;
     a.cap_units = pl.cap_units;
+    a.umap = pgb_unit_map(ctx, ucnt, np, pl.cap_units);
     a.out_base = pl.out_base;
     a.lds_bytes = pl.lds_bytes;
     a.log2cap = 6;

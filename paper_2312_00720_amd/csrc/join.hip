@@ -114,16 +114,26 @@ __global__ void k_unit_count(const uint32_t *__restrict__ rpo, const uint32_t *_
                              uint32_t np, uint32_t rc, uint32_t spiece, uint32_t *__restrict__ ucnt,
                              uint32_t *__restrict__ flags) {
     unsigned long long *total = reinterpret_cast<unsigned long long *>(flags + 4);
+    unsigned long long sum = 0;
+    uint32_t most = 0;
     for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < np; p += gridDim.x * blockDim.x) {
         const uint32_t nr = rpo[p + 1] - rpo[p], ns = spo[p + 1] - spo[p];
         const uint64_t units = (nr && ns) ? (uint64_t)ceil_div_u32(nr, rc) * ceil_div_u32(ns, spiece) : 0ull;
         ucnt[p] = (uint32_t)min<uint64_t>(units, kMaxUnits);
-        if (units) {
-            const unsigned long long before = atomicAdd(total, (unsigned long long)units);
-            if (before + units > kMaxUnits) atomicOr(&flags[3], 1u);
-        }
-        if (nr > rc && ns) atomicOr(&flags[0], 1u);  // a partition spans several R blocks
-        if (ns) atomicMax(&flags[2], nr);
+        sum += units;
+        if (ns) most = max(most, nr);
+    }
+    // one set of atomics per wave
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+        sum += __shfl_xor(sum, d, kWave);
+        most = max(most, (uint32_t)__shfl_xor(most, d, kWave));
+    }
+    if (lane_id() == 0 && sum) {
+        const unsigned long long before = atomicAdd(total, sum);
+        if (before + sum > kMaxUnits) atomicOr(&flags[3], 1u);
+        if (most > rc) atomicOr(&flags[0], 1u);  // a partition spans several R blocks
+        atomicMax(&flags[2], most);
     }
 }
 
