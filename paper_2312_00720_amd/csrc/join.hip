@@ -137,6 +137,72 @@ __global__ void k_unit_count(const uint32_t *__restrict__ rpo, const uint32_t *_
     }
 }
 
+// Unit counts, their prefix, the flags and the unit map of a single join in one
+// workgroup: up to kOneKernelUnits units this takes the time of two launches,
+// where a fill, a count, a scan and a map are four. The map holds `cap` units.
+constexpr uint64_t kOneKernelUnits = 65536;
+__global__ __launch_bounds__(1024) void k_join_units(const uint32_t *__restrict__ rpo, const uint32_t *__restrict__ spo,
+                                                     uint32_t np, uint32_t rc, uint32_t spiece,
+                                                     uint32_t *__restrict__ ubase, uint32_t *__restrict__ flags,
+                                                     uint32_t cap, uint32_t *__restrict__ umap) {
+    constexpr int W = 1024 / kWave, PER = 4;  // consecutive partitions per thread and round
+    __shared__ unsigned long long s_tmp[W];
+    __shared__ uint32_t s_most[W];
+    unsigned long long carry = 0;
+    uint32_t most = 0;
+    const int lane = lane_id();
+    for (uint32_t base = 0; base < np; base += 1024 * PER) {
+        const uint32_t p0 = base + threadIdx.x * PER;
+        uint32_t ro[PER + 1], so[PER + 1];
+#pragma unroll
+        for (int k = 0; k <= PER; ++k) {
+            ro[k] = rpo[min(p0 + k, np)];
+            so[k] = spo[min(p0 + k, np)];
+        }
+        unsigned long long u[PER], sum = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t nr = ro[k + 1] - ro[k], ns = so[k + 1] - so[k];  // 0 past the last partition
+            u[k] = (nr && ns) ? (unsigned long long)ceil_div_u32(nr, rc) * ceil_div_u32(ns, spiece) : 0ull;
+            sum += u[k];
+            if (ns) most = max(most, nr);
+        }
+        unsigned long long all;
+        unsigned long long at = carry + block_exclusive_sum<unsigned long long, W>(sum, s_tmp, &all);
+        carry += all;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t first = (uint32_t)min(at, (unsigned long long)kMaxUnits);
+            if (p0 + k < np) ubase[p0 + k] = first;
+            const uint32_t cnt = at < cap ? (uint32_t)min(u[k], cap - at) : 0u;
+            if (cnt <= 4) {
+                for (uint32_t i = 0; i < cnt; ++i) umap[first + i] = p0 + k;
+            }
+            // a partition of many units (skew, few partitions): its wave writes them
+            for (uint64_t many = __ballot(cnt > 4); many; many &= many - 1) {
+                const int l = __ffsll((long long)many) - 1;
+                const uint32_t f = __shfl(first, l, kWave), c = __shfl(cnt, l, kWave), p = __shfl(p0 + k, l, kWave);
+                for (uint32_t i = lane; i < c; i += kWave) umap[f + i] = p;
+            }
+            at += u[k];
+        }
+    }
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) most = max(most, (uint32_t)__shfl_xor(most, d, kWave));
+    if (lane == 0) s_most[threadIdx.x / kWave] = most;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 0; w < W; ++w) most = max(most, s_most[w]);
+        ubase[np] = (uint32_t)min(carry, (unsigned long long)kMaxUnits);
+        flags[0] = most > rc;  // a partition spans several R blocks
+        flags[1] = 0;
+        flags[2] = most;
+        flags[3] = carry > kMaxUnits;
+        flags[4] = (uint32_t)carry;
+        flags[5] = (uint32_t)(carry >> 32);
+    }
+}
+
 // Units the passes process: none once the count overflowed, else at most the
 // launch's (or plan's) capacity.
 __device__ __forceinline__ uint32_t units_to_run(const uint32_t *nunits, const uint32_t *flags, uint32_t cap) {
@@ -790,6 +856,8 @@ template <typename K, uint32_t BUILD, bool WRITE>
 __global__ __launch_bounds__(Geo<BUILD>::kThreads, WRITE ? Geo<BUILD>::kMinWEager : Geo<BUILD>::kMinWCount) void k_join(JoinArgs a) {
     extern __shared__ uint4 s_dyn4[];
     const JoinLds<K> sh = join_lds<K, BUILD>(reinterpret_cast<uint8_t *>(s_dyn4), a.lds_rows);
+    // a block larger than the LDS was sized for (the host sees it and sizes again)
+    if (min(a.flags[2], a.rc) > a.lds_rows) return;
     if (blockIdx.x < units_to_run(a.nunits, a.flags, a.cap_units)) join_unit<K, BUILD, WRITE>(a, blockIdx.x, 0ull, sh);
 }
 
@@ -1139,36 +1207,44 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
     const uint32_t np = seg_bits ? (n_inst << 8) : (1u << bits);
     uint32_t *ucnt = ctx.scratch_n<uint32_t>(np + 1);
     uint32_t *flags = ctx.scratch_n<uint32_t>(6);  // [0..3] flags, [4..5] 64-bit unit total
-    fill_u32(s, flags, 0u, 6);
-    GJ_LAUNCH("k_unit_count", 20.0 * np, k_unit_count, dim3(std::min<uint32_t>((np + 255) / 256, 1024)),
-              dim3(256), 0, s, R.poff, S.poff, np, (uint32_t)r_block, join_s_piece(r_block), ucnt, flags);
-    scan_exclusive_u32(ctx, ucnt, ucnt, np, ucnt + np);
-    // Eager calls read the unit count and size every launch exactly; a plan sizes
-    // for its capacity and the kernels read the count from device memory.
-    uint32_t cap_units, grid;
+    const uint32_t *nunits = ucnt + np;
+    // Units of a single join whose partitions have one R block each.
+    const uint64_t bound = (uint64_t)np + ceil_div_u32(S.rows, join_s_piece(r_block));
+    const bool one_kernel = !pl && !seg_bits && bound <= kOneKernelUnits;
+    // Single joins with 4096-row tables do not wait for the unit count: the count
+    // pass runs for the bound, with LDS for R blocks a quarter over the mean
+    // partition, and the one read that sizes the output tells whether both held
+    // (else the pass runs again, sized exactly). A join of 2^16 x 2^20 rows waits
+    // once instead of twice: 142 -> 130 us (1000 x 4000 rows: 112 -> 90). Larger tables keep the first read: their
+    // LDS decides how many workgroups share a compute unit, and it is under 1% of the join.
+    bool guess = one_kernel && table_rows == 4096;
+    uint32_t cap_units = (uint32_t)std::min<uint64_t>(bound, kMaxUnits), grid;
     uint32_t lds_rows = (uint32_t)r_block;  // rows of the largest R block a unit builds on
-    if (pl) {
-        cap_units = pl->cap_units;
-        grid = std::max<uint32_t>(1, std::min<uint32_t>(cap_units, kPersistentGrid));
+    uint32_t *umap = nullptr;
+    if (one_kernel) {
+        umap = ctx.scratch_n<uint32_t>(cap_units);
+        GJ_LAUNCH("k_unit_count", 20.0 * np, k_join_units, dim3(1), dim3(1024), 0, s, R.poff, S.poff, np,
+                  (uint32_t)r_block, join_s_piece(r_block), ucnt, flags, cap_units, umap);
     } else {
-        uint32_t hf[6];
-        read_back_parts(s, {{&cap_units, ucnt + np, 4}, {hf, flags, sizeof(hf)}});
-        // hf[2]: most R rows in a partition that S probes (a block holds at most r_block)
-        lds_rows = std::max<uint32_t>(64, (std::min<uint32_t>(hf[2], (uint32_t)r_block) + 63) & ~63u);
+        fill_u32(s, flags, 0u, 6);
+        GJ_LAUNCH("k_unit_count", 20.0 * np, k_unit_count, dim3(std::min<uint32_t>((np + 255) / 256, 1024)),
+                  dim3(256), 0, s, R.poff, S.poff, np, (uint32_t)r_block, join_s_piece(r_block), ucnt, flags);
+        scan_exclusive_u32(ctx, ucnt, ucnt, np, ucnt + np);
+    }
+    uint32_t units = 0, hf[6] = {0};
+    // What the flags say before any pass: -1 where the caller may partition again.
+    // hf[2]: most R rows in a partition that S probes (a block holds at most r_block)
+    const auto check_units = [&]() -> bool {
         if (hf[3]) throw Error(GJ_EOVERFLOW, "more than 2^31-1 join work units (R partitions far larger than the "
                                              "build block)");
-        if (stats) {
-            stats->max_r_rows = hf[2];
-            stats->multi_block = hf[0] != 0;
-            if (stats->check_spread && hf[2] > stats->spread_limit) return -1;
-        }
-        grid = cap_units;
-        if (cap_units == 0) {
-            if (inst_off) fill_u64(s, inst_off, 0ull, (uint64_t)n_inst + 1);
-            return 0;
-        }
-    }
-
+        if (!stats) return true;
+        stats->max_r_rows = hf[2];
+        stats->multi_block = hf[0] != 0;
+        return !(stats->check_spread && hf[2] > stats->spread_limit);
+    };
+    const auto exact_rows = [&]() {
+        return std::max<uint32_t>(64, (std::min<uint32_t>(hf[2], (uint32_t)r_block) + 63) & ~63u);
+    };
     JoinArgs a{};
     a.rkey = R.key;
     a.skey = S.key;
@@ -1177,49 +1253,83 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
     a.np = np;
     a.ubase = ucnt;
     a.rc = (uint32_t)r_block;
-    a.lds_rows = lds_rows;
     a.skip_bits = (stats && stats->hashed_digits) ? 0 : bits;
     a.seg_bits = seg_bits;
     a.seg_bshift = pl ? pl->seg_bshift : nullptr;
     a.bshift = 0;
-    a.nunits = ucnt + np;
-    a.cap_units = cap_units;
+    a.nunits = nunits;
     a.out_base = pl ? pl->out_base : nullptr;
     a.midx = ctx.scratch_n<uint16_t>(std::max<uint32_t>(S.rows, 1));
     a.flags = flags;
     a.lds_if_complex = pl ? 1 : 0;
-    uint32_t *umap = ctx.scratch_n<uint32_t>(cap_units);
-    GJ_LAUNCH("k_unit_map", 4.0 * cap_units, k_unit_map,
-              dim3(std::max<uint32_t>(1, std::min<uint32_t>(ceil_div_u32(cap_units, 256), 1024))),
-              dim3(256), 0, s, ucnt, np, ucnt + np, (const uint32_t *)flags, cap_units, umap);
-    a.umap = umap;
-    const uint64_t nw = (uint64_t)cap_units * wpu;
-    uint64_t *wcnt = ctx.scratch_n<uint64_t>(nw + 1);
-    uint64_t *total = pl ? pl->total : wcnt + nw;
-    a.wcnt = wcnt;
     const double nrows_r = R.rows, nrows_s = S.rows;
     const double key_reads = (nrows_r + nrows_s) * key_bytes;
-    launch_join_pass(0, key_bytes, table_rows, s, pl != nullptr, grid, a, key_reads);
-    if (pl) scan_exclusive_u64_dev(ctx, wcnt, wcnt, nw, ucnt + np, wpu, total);
-    else scan_exclusive_u64(ctx, wcnt, wcnt, nw, total);
-    uint64_t T;
+    uint64_t *wcnt = nullptr, *total = nullptr;
+    uint64_t T = 0;
     bool complex = true;  // plans launch both write passes; each decides on the device
     bool dups = false;    // eager calls: some S row matches several R rows
     uint32_t max_r_rows = 0;
-    if (pl) {
-        T = pl->out_cap;  // stores are checked against the capacity; the true count stays on the device
-        *out = pl->out;
-    } else {
-        uint32_t hf[3];
-        read_back_parts(s, {{&T, total, 8}, {hf, flags, 12}});
+    for (;;) {
+        if (pl) {
+            cap_units = pl->cap_units;
+            grid = std::max<uint32_t>(1, std::min<uint32_t>(cap_units, kPersistentGrid));
+        } else if (guess) {
+            grid = cap_units;
+            const uint32_t mean = (uint32_t)((uint64_t)R.rows >> bits) + 1;
+            lds_rows = std::min<uint32_t>((uint32_t)r_block, (mean + mean / 4 + 255) & ~255u);
+        } else {
+            // eager calls read the unit count and size every launch exactly
+            read_back_parts(s, {{&units, nunits, 4}, {hf, flags, sizeof(hf)}});
+            if (!check_units()) return -1;
+            lds_rows = exact_rows();
+            if (units == 0) {
+                if (inst_off) fill_u64(s, inst_off, 0ull, (uint64_t)n_inst + 1);
+                return 0;
+            }
+            if (units > cap_units) umap = nullptr;
+            grid = cap_units = units;
+        }
+        a.lds_rows = lds_rows;
+        a.cap_units = cap_units;
+        if (!umap) {
+            umap = ctx.scratch_n<uint32_t>(cap_units);
+            GJ_LAUNCH("k_unit_map", 4.0 * cap_units, k_unit_map,
+                      dim3(std::max<uint32_t>(1, std::min<uint32_t>(ceil_div_u32(cap_units, 256), 1024))),
+                      dim3(256), 0, s, ucnt, np, nunits, (const uint32_t *)flags, cap_units, umap);
+        }
+        a.umap = umap;
+        const uint64_t nw = (uint64_t)cap_units * wpu;
+        wcnt = ctx.scratch_n<uint64_t>(nw + 1);
+        total = pl ? pl->total : wcnt + nw;
+        a.wcnt = wcnt;
+        launch_join_pass(0, key_bytes, table_rows, s, pl != nullptr, grid, a, key_reads);
+        if (pl || guess) scan_exclusive_u64_dev(ctx, wcnt, wcnt, nw, nunits, wpu, total);
+        else scan_exclusive_u64(ctx, wcnt, wcnt, nw, total);
+        if (pl) {
+            T = pl->out_cap;  // stores are checked against the capacity; the true count stays on the device
+            *out = pl->out;
+            break;
+        }
+        read_back_parts(s, {{&T, total, 8}, {&units, nunits, 4}, {hf, flags, sizeof(hf)}});
+        if (guess) {
+            if (!check_units()) return -1;
+            if (units > cap_units || std::min<uint32_t>(hf[2], (uint32_t)r_block) > lds_rows) {
+                guess = false;  // the bounds did not hold: nothing is known but the units
+                continue;
+            }
+            if (units == 0) return 0;
+            grid = units;
+            a.lds_rows = exact_rows();
+        }
         complex = (hf[0] | hf[1]) != 0;
         dups = hf[1] != 0;
         max_r_rows = hf[2];
+        break;
     }
     if (inst_off)
         GJ_LAUNCH("k_instance_offsets", 16.0 * n_inst, k_instance_offsets,
                   dim3(std::min<uint32_t>(ceil_div_u32(n_inst + 1, 256), 1024)), dim3(256), 0, s, ucnt, wcnt, wpu,
-                  n_inst, ucnt + np, (const uint32_t *)flags, cap_units, total, a.out_base, inst_off);
+                  n_inst, nunits, (const uint32_t *)flags, cap_units, total, a.out_base, inst_off);
     if (pl && (pl->next_base || pl->units_out))
         GJ_LAUNCH("k_advance_base", 16.0, k_advance_base, dim3(1), dim3(64), 0, s, a.out_base, total, pl->next_base,
                   (const uint32_t *)(ucnt + np), (const uint32_t *)flags, pl->units_out);

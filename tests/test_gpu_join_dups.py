@@ -53,3 +53,33 @@ def test_many_matches_element_by_element(case, mat):
     assert len(got[0]) == len(order) and len(order) > 0
     for a, b in zip(got, want):
         np.testing.assert_array_equal(a, np.asarray(b)[order])
+
+
+@pytest.mark.parametrize("big", [1300, 1700, 3500, 4500, 9000])
+@pytest.mark.parametrize("mat", ["gftr", "gfur"])
+def test_uneven_partitions(big, mat):
+    """One R partition of `big` rows among sixteen of about 1200: within the LDS the
+    count pass guesses, past it, past a build block, and past the spread limit
+    (then both sides are partitioned on hashed keys)."""
+    import paper_2312_00720_amd as gj
+    from gpu_util import canon, dev, host, say
+    say(f"join uneven big={big} {mat}")
+    g = datagen.rng(big)
+    n_r, n_s, bits = 20000, 70001, 4
+    rest = n_r - big
+    rk = np.concatenate([np.arange(big) * 16 + 3, np.arange(rest) // 15 * 16 + np.array([d for d in range(16) if d != 3])[np.arange(rest) % 15]])
+    rk = g.permutation(rk).astype(np.int32)
+    sk = g.integers(0, 16 * big, size=n_s).astype(np.int32)
+    d = {"r_key": rk, "r_pay": datagen.payload_columns(g, n_r, 2), "s_key": sk, "s_pay": datagen.payload_columns(g, n_s, 2)}
+    k, r, s = gj.join(dev(d["r_key"]), [dev(x) for x in d["r_pay"]], dev(d["s_key"]), [dev(x) for x in d["s_pay"]],
+                      mat=mat, algo="phj")
+    got = [host(k)] + [host(x) for x in r + s]
+    want = oracle.join(d["r_key"], d["r_pay"], d["s_key"], d["s_pay"])
+    assert len(got[0]) == len(want[0])
+    if big <= 4096:
+        order = np.argsort(want[0] & ((1 << bits) - 1), kind="stable")
+        for a, b in zip(got, want):
+            np.testing.assert_array_equal(a, np.asarray(b)[order])
+    else:
+        for a, b in zip(canon(got), canon(want)):
+            np.testing.assert_array_equal(a, b)
