@@ -37,22 +37,24 @@ constexpr uint32_t kPersistentGrid = 4096;  // workgroups of a plan's count and 
 // rows: 2048 for 4096 rows, whose 32 KB of LDS then let four workgroups share a
 // compute unit; 4096 for 8192 rows; 8192 for 16384) and probe rounds in flight
 // per lane (the larger shapes have at most 128 registers per lane).
-template <uint32_t BUILD>
+template <uint32_t BUILD, int NT>
 struct Geo {
     static constexpr uint32_t kBuild = BUILD;
-    static constexpr int kThreads = (int)(BUILD / 16);
+    static constexpr int kThreads = NT;
     static constexpr int kWv = kThreads / kWave;
     static constexpr uint32_t kSPiece = 2 * BUILD;
     static constexpr int kMaxLog2nb = BUILD >= 16384 ? 13 : (BUILD == 4096 ? 11 : 12);
     static constexpr uint32_t kMaxNb = 1u << kMaxLog2nb;
-    static constexpr int kPB = BUILD == 16384 ? 8 : 16;  // count pass
-    static constexpr int kPBWrite = BUILD == 4096 ? 16 : 8;  // LDS write pass
+    static constexpr int kRows = (int)BUILD / NT;  // table rows per thread
+    static constexpr int kPB = BUILD == 16384 || kRows < 16 ? 8 : 16;  // count pass
+    static constexpr int kPBWrite = BUILD == 4096 && kRows == 16 ? 16 : 8;  // LDS write pass
+    static constexpr int kPBStream = kRows < 16 ? 8 : 16;  // streaming write passes
     // waves per SIMD the register allocation must allow: the persistent
     // kernels and the one-unit-per-workgroup kernels (two 512-thread
     // workgroups per compute unit)
     static constexpr int kMinW = 4;
     static constexpr int kMinWWrite = BUILD == 4096 ? 3 : 4;
-    static constexpr int kMinWEager = BUILD == 4096 ? 1 : 4;
+    static constexpr int kMinWEager = BUILD == 4096 ? 1 : 4;  // (1024 threads: at least 4 by themselves)
     // the eager count pass: two 1024-thread workgroups per compute unit when their
     // LDS (sized by the largest R block) fits twice
     static constexpr int kMinWCount = BUILD == 16384 ? 8 : kMinWEager;
@@ -336,12 +338,12 @@ struct JoinLds {
     int *is_long;
 };
 constexpr size_t align8(size_t x) { return (x + 7) & ~(size_t)7; }
-template <typename K, uint32_t BUILD>
+template <typename K, uint32_t BUILD, int NT>
 constexpr size_t join_lds_bytes(uint32_t rows) {
-    return align8((size_t)rows * sizeof(K)) + align8((size_t)rows * 2) + align8(((size_t)Geo<BUILD>::kMaxNb + 1) * 2) +
-           4 * ((size_t)Geo<BUILD>::kWv + 8);
+    return align8((size_t)rows * sizeof(K)) + align8((size_t)rows * 2) + align8(((size_t)Geo<BUILD, NT>::kMaxNb + 1) * 2) +
+           4 * ((size_t)Geo<BUILD, NT>::kWv + 8);
 }
-template <typename K, uint32_t BUILD>
+template <typename K, uint32_t BUILD, int NT>
 __device__ __forceinline__ JoinLds<K> join_lds(uint8_t *p, uint32_t rows) {
     JoinLds<K> L;
     L.rkey = reinterpret_cast<K *>(p);
@@ -349,9 +351,9 @@ __device__ __forceinline__ JoinLds<K> join_lds(uint8_t *p, uint32_t rows) {
     L.entry = reinterpret_cast<uint16_t *>(p);
     p += align8((size_t)rows * 2);
     L.b = reinterpret_cast<uint16_t *>(p);
-    p += align8(((size_t)Geo<BUILD>::kMaxNb + 1) * 2);
+    p += align8(((size_t)Geo<BUILD, NT>::kMaxNb + 1) * 2);
     L.tmp = reinterpret_cast<uint32_t *>(p);
-    L.unit = L.tmp + Geo<BUILD>::kWv;
+    L.unit = L.tmp + Geo<BUILD, NT>::kWv;
     L.is_long = reinterpret_cast<int *>(L.unit + 6);
     return L;
 }
@@ -419,9 +421,9 @@ __device__ __forceinline__ void decode_unit(const JoinArgs &a, uint32_t u, uint3
 
 // Inclusive scan of the nb bucket counts in s_b (s_b[b] = end of bucket b), and
 // s_b[nb] = rn.
-template <uint32_t BUILD>
+template <uint32_t BUILD, int NT>
 __device__ __forceinline__ void scan_buckets(uint16_t *s_b, uint32_t *s_tmp, uint32_t nb, uint32_t rn) {
-    using G = Geo<BUILD>;
+    using G = Geo<BUILD, NT>;
     constexpr int per = (int)((G::kMaxNb + G::kThreads - 1) / G::kThreads);
     const uint32_t first = threadIdx.x * per;
     uint32_t v[per];
@@ -445,9 +447,9 @@ __device__ __forceinline__ void scan_buckets(uint16_t *s_b, uint32_t *s_tmp, uin
 // The table is built straight into bucket order from registers (the R keys of
 // this thread: counts, scan, placement), since counts need no ordered chains;
 // the wave's first round of S keys loads during the build.
-template <typename K, uint32_t BUILD>
+template <typename K, uint32_t BUILD, int NT>
 __device__ __forceinline__ void count_unit(const JoinArgs &a, uint32_t u, const JoinLds<K> &sh) {
-    using G = Geo<BUILD>;
+    using G = Geo<BUILD, NT>;
     constexpr int PB = G::kPB;
     constexpr int kT = G::kThreads;
     constexpr int kWv = G::kWv;
@@ -486,7 +488,7 @@ __device__ __forceinline__ void count_unit(const JoinArgs &a, uint32_t u, const 
     for (int k = 0; k < PER; ++k)
         if ((uint32_t)(tid + k * kT) < rn) b16_add1(s_b, bucket_of<K>(kr[k], skip_bits, log2nb));
     __syncthreads();
-    scan_buckets<BUILD>(s_b, sh.tmp, nb, rn);
+    scan_buckets<BUILD, NT>(s_b, sh.tmp, nb, rn);
     __syncthreads();
     // placement from the end of each bucket; afterwards s_b[b] = start of bucket b
 #pragma unroll
@@ -650,9 +652,9 @@ __device__ __forceinline__ void write_dups(const JoinArgs &a, const JoinLds<K> &
 // Write pass of unit u on the LDS table (the general case: partitions spanning
 // several R blocks, or S rows with several matches): build with chains in row
 // order, probe, and write every match at the positions the count pass sized.
-template <typename K, uint32_t BUILD>
+template <typename K, uint32_t BUILD, int NT>
 __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64_t out_base, const JoinLds<K> &sh) {
-    using G = Geo<BUILD>;
+    using G = Geo<BUILD, NT>;
     constexpr int PB = G::kPBWrite;
     constexpr int kBlockT = G::kThreads;
     constexpr int kWv = G::kWv;
@@ -682,7 +684,7 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
     __syncthreads();
     for (uint32_t i = tid; i < rn; i += kBlockT) b16_add1(s_b, bucket_of<K>(s_rkey[i], skip_bits, log2nb));
     __syncthreads();
-    scan_buckets<BUILD>(s_b, sh.tmp, nb, rn);
+    scan_buckets<BUILD, NT>(s_b, sh.tmp, nb, rn);
     __syncthreads();
     // placement from the end of each bucket; afterwards s_b[b] = start of bucket b
     for (uint32_t i = tid; i < rn; i += kBlockT) {
@@ -845,20 +847,20 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
     }
 }
 
-template <typename K, uint32_t BUILD, bool WRITE>
+template <typename K, uint32_t BUILD, int NT, bool WRITE>
 __device__ __forceinline__ void join_unit(const JoinArgs &a, uint32_t u, uint64_t out_base, const JoinLds<K> &sh) {
-    if constexpr (WRITE) write_unit<K, BUILD>(a, u, out_base, sh);
-    else count_unit<K, BUILD>(a, u, sh);
+    if constexpr (WRITE) write_unit<K, BUILD, NT>(a, u, out_base, sh);
+    else count_unit<K, BUILD, NT>(a, u, sh);
 }
 
 // One work unit per workgroup (eager calls: the grid is the unit count).
-template <typename K, uint32_t BUILD, bool WRITE>
-__global__ __launch_bounds__(Geo<BUILD>::kThreads, WRITE ? Geo<BUILD>::kMinWEager : Geo<BUILD>::kMinWCount) void k_join(JoinArgs a) {
+template <typename K, uint32_t BUILD, int NT, bool WRITE>
+__global__ __launch_bounds__(NT, (WRITE ? Geo<BUILD, NT>::kMinWEager : Geo<BUILD, NT>::kMinWCount)) void k_join(JoinArgs a) {
     extern __shared__ uint4 s_dyn4[];
-    const JoinLds<K> sh = join_lds<K, BUILD>(reinterpret_cast<uint8_t *>(s_dyn4), a.lds_rows);
+    const JoinLds<K> sh = join_lds<K, BUILD, NT>(reinterpret_cast<uint8_t *>(s_dyn4), a.lds_rows);
     // a block larger than the LDS was sized for (the host sees it and sizes again)
     if (min(a.flags[2], a.rc) > a.lds_rows) return;
-    if (blockIdx.x < units_to_run(a.nunits, a.flags, a.cap_units)) join_unit<K, BUILD, WRITE>(a, blockIdx.x, 0ull, sh);
+    if (blockIdx.x < units_to_run(a.nunits, a.flags, a.cap_units)) join_unit<K, BUILD, NT, WRITE>(a, blockIdx.x, 0ull, sh);
 }
 
 // Write pass without a hash table, for the common case recorded by the count
@@ -868,10 +870,10 @@ __global__ __launch_bounds__(Geo<BUILD>::kThreads, WRITE ? Geo<BUILD>::kMinWEage
 // partition-local R rows; GFUR: original rows through the row ids). It needs no
 // LDS, so it always runs 256-thread workgroups whose waves take the count
 // pass's (unit, wave) slots one by one, whatever the table shape.
-template <typename K, uint32_t BUILD, bool GFUR>
+template <typename K, uint32_t BUILD, int NT, bool GFUR>
 __global__ __launch_bounds__(kBlock, GFUR ? 4 : 1) void k_join_stream(JoinArgs a) {
-    using G = Geo<BUILD>;
-    constexpr int PB = 16;
+    using G = Geo<BUILD, NT>;
+    constexpr int PB = G::kPBStream;
     constexpr int kWv = G::kWv;
     constexpr uint32_t kSPiece = G::kSPiece;
     if (a.flags[0] | a.flags[1]) return;  // the LDS write pass handles this input
@@ -947,10 +949,10 @@ __global__ __launch_bounds__(kBlock, GFUR ? 4 : 1) void k_join_stream(JoinArgs a
 // fewer rows than its R block (cold partitions under skew) gathers from HBM
 // instead, since staging would move more bytes than it saves. Launched when
 // the largest partition's R payload fits the dynamic LDS.
-template <typename K, uint32_t BUILD>
-__global__ __launch_bounds__(Geo<BUILD>::kThreads, Geo<BUILD>::kMinWStaged) void k_join_stream_staged(JoinArgs a) {
-    using G = Geo<BUILD>;
-    constexpr int PB = 16;
+template <typename K, uint32_t BUILD, int NT>
+__global__ __launch_bounds__(NT, (Geo<BUILD, NT>::kMinWStaged)) void k_join_stream_staged(JoinArgs a) {
+    using G = Geo<BUILD, NT>;
+    constexpr int PB = G::kPBStream;
     constexpr int kWv = G::kWv;
     constexpr int kT = G::kThreads;
     constexpr uint32_t kSPiece = G::kSPiece;
@@ -1082,15 +1084,15 @@ __global__ __launch_bounds__(Geo<BUILD>::kThreads, Geo<BUILD>::kMinWStaged) void
 }
 
 // Persistent workgroups over the unit count held in device memory (plans).
-template <typename K, uint32_t BUILD, bool WRITE>
-__global__ __launch_bounds__(Geo<BUILD>::kThreads, WRITE ? Geo<BUILD>::kMinWWrite : Geo<BUILD>::kMinW) void k_join_persist(JoinArgs a) {
+template <typename K, uint32_t BUILD, int NT, bool WRITE>
+__global__ __launch_bounds__(NT, (WRITE ? Geo<BUILD, NT>::kMinWWrite : Geo<BUILD, NT>::kMinW)) void k_join_persist(JoinArgs a) {
     extern __shared__ uint4 s_dyn4[];
-    const JoinLds<K> sh = join_lds<K, BUILD>(reinterpret_cast<uint8_t *>(s_dyn4), a.lds_rows);
+    const JoinLds<K> sh = join_lds<K, BUILD, NT>(reinterpret_cast<uint8_t *>(s_dyn4), a.lds_rows);
     if (WRITE && a.lds_if_complex && !(a.flags[0] | a.flags[1])) return;  // the streaming pass writes
     const uint32_t n_units = units_to_run(a.nunits, a.flags, a.cap_units);
     const uint64_t out_base = a.out_base ? *a.out_base : 0ull;
     for (uint32_t u = blockIdx.x; u < n_units; u += gridDim.x) {
-        join_unit<K, BUILD, WRITE>(a, u, out_base, sh);
+        join_unit<K, BUILD, NT, WRITE>(a, u, out_base, sh);
         __syncthreads();  // the unit's LDS state is rebuilt by the next one
     }
 }
@@ -1124,26 +1126,31 @@ __global__ void k_advance_base(const uint64_t *__restrict__ base, const uint64_t
 }
 
 // The count and write kernels of one table shape.
-template <typename K, uint32_t BUILD>
+template <typename K, uint32_t BUILD, int NT>
 struct JoinKernels {
-    using G = Geo<BUILD>;
+    using G = Geo<BUILD, NT>;
     static void count(hipStream_t s, bool planned, uint32_t grid, const JoinArgs &a, double bytes) {
-        const size_t shm = join_lds_bytes<K, BUILD>(a.lds_rows);
-        if (planned) GJ_LAUNCH("k_join_count", bytes, (k_join_persist<K, BUILD, false>), dim3(grid), dim3(G::kThreads), shm, s, a);
-        else GJ_LAUNCH("k_join_count", bytes, (k_join<K, BUILD, false>), dim3(grid), dim3(G::kThreads), shm, s, a);
+        const size_t shm = join_lds_bytes<K, BUILD, NT>(a.lds_rows);
+        if constexpr (G::kRows == 16) {
+            if (planned) {
+                GJ_LAUNCH("k_join_count", bytes, (k_join_persist<K, BUILD, NT, false>), dim3(grid), dim3(G::kThreads), shm, s, a);
+                return;
+            }
+        }
+        GJ_LAUNCH("k_join_count", bytes, (k_join<K, BUILD, NT, false>), dim3(grid), dim3(G::kThreads), shm, s, a);
     }
     // grid: workgroups of the unit passes; the streaming pass has kWaves-wave workgroups
     static void stream(hipStream_t s, uint32_t grid, const JoinArgs &a, double bytes) {
         grid = (uint32_t)std::min<uint64_t>((uint64_t)grid * G::kWv / kWaves, 1u << 30);
-        if (a.srow) GJ_LAUNCH("k_join_write", bytes, (k_join_stream<K, BUILD, true>), dim3(grid), dim3(kBlock), 0, s, a);
-        else GJ_LAUNCH("k_join_write", bytes, (k_join_stream<K, BUILD, false>), dim3(grid), dim3(kBlock), 0, s, a);
+        if (a.srow) GJ_LAUNCH("k_join_write", bytes, (k_join_stream<K, BUILD, NT, true>), dim3(grid), dim3(kBlock), 0, s, a);
+        else GJ_LAUNCH("k_join_write", bytes, (k_join_stream<K, BUILD, NT, false>), dim3(grid), dim3(kBlock), 0, s, a);
     }
     static void staged(hipStream_t s, uint32_t grid, size_t shm, const JoinArgs &a, double bytes) {
-        GJ_LAUNCH("k_join_write", bytes, (k_join_stream_staged<K, BUILD>), dim3(grid), dim3(G::kThreads), shm, s, a);
+        GJ_LAUNCH("k_join_write", bytes, (k_join_stream_staged<K, BUILD, NT>), dim3(grid), dim3(G::kThreads), shm, s, a);
     }
     // R payload columns beside the table, as many as fit (S rows with several matches)
     static size_t stage_r(JoinArgs &a) {
-        size_t shm = join_lds_bytes<K, BUILD>(a.lds_rows), used = 0;
+        size_t shm = join_lds_bytes<K, BUILD, NT>(a.lds_rows), used = 0;
         for (; a.rstaged < a.nr; ++a.rstaged) {
             const size_t b = ((size_t)a.lds_rows * a.rw[a.rstaged] + 15) & ~(size_t)15;
             if (shm + used + b > kJoinWriteLds) break;
@@ -1153,36 +1160,55 @@ struct JoinKernels {
         return shm + used;
     }
     static void write_lds(hipStream_t s, bool planned, uint32_t grid, JoinArgs a, double bytes, bool dups) {
-        const size_t shm = dups ? stage_r(a) : join_lds_bytes<K, BUILD>(a.lds_rows);
-        if (planned) GJ_LAUNCH("k_join_write_lds", bytes, (k_join_persist<K, BUILD, true>), dim3(grid), dim3(G::kThreads), shm, s, a);
-        else GJ_LAUNCH("k_join_write_lds", bytes, (k_join<K, BUILD, true>), dim3(grid), dim3(G::kThreads), shm, s, a);
+        const size_t shm = dups ? stage_r(a) : join_lds_bytes<K, BUILD, NT>(a.lds_rows);
+        if constexpr (G::kRows == 16) {
+            if (planned) {
+                GJ_LAUNCH("k_join_write_lds", bytes, (k_join_persist<K, BUILD, NT, true>), dim3(grid), dim3(G::kThreads), shm, s, a);
+                return;
+            }
+        }
+        GJ_LAUNCH("k_join_write_lds", bytes, (k_join<K, BUILD, NT, true>), dim3(grid), dim3(G::kThreads), shm, s, a);
     }
 };
 
 // Pass 0 = count, 1 = streaming write, 2 = LDS write, 3 = streaming write with
 // the R side staged in shm bytes of LDS; the table shape holds r_block rows. Pass 2
 // with shm != 0: S rows match several R rows, R payloads may be staged.
-void launch_join_pass(int pass, int key_bytes, uint32_t table_rows, hipStream_t s, bool planned, uint32_t grid,
-                      const JoinArgs &a, double bytes, size_t shm = 0) {
-#define GJ_JP(K, B)                                                 \
+// waves: of a unit (waves_per_unit).
+void launch_join_pass(int pass, int key_bytes, uint32_t table_rows, uint32_t waves, hipStream_t s, bool planned,
+                      uint32_t grid, const JoinArgs &a, double bytes, size_t shm = 0) {
+#define GJ_JP(K, B, NT)                                             \
     do {                                                            \
-        if (pass == 0) JoinKernels<K, B>::count(s, planned, grid, a, bytes);     \
-        else if (pass == 1) JoinKernels<K, B>::stream(s, grid, a, bytes);        \
-        else if (pass == 3) JoinKernels<K, B>::staged(s, grid, shm, a, bytes);   \
-        else JoinKernels<K, B>::write_lds(s, planned, grid, a, bytes, shm != 0); \
+        if (pass == 0) JoinKernels<K, B, NT>::count(s, planned, grid, a, bytes);     \
+        else if (pass == 1) JoinKernels<K, B, NT>::stream(s, grid, a, bytes);        \
+        else if (pass == 3) JoinKernels<K, B, NT>::staged(s, grid, shm, a, bytes);   \
+        else JoinKernels<K, B, NT>::write_lds(s, planned, grid, a, bytes, shm != 0); \
     } while (0)
     if (key_bytes == 4) {
-        if (table_rows == 4096) GJ_JP(int32_t, 4096);
-        else if (table_rows == 8192) GJ_JP(int32_t, 8192);
-        else GJ_JP(int32_t, 16384);
+        if (table_rows == 4096 && waves == 16) GJ_JP(int32_t, 4096, 1024);
+        else if (table_rows == 4096) GJ_JP(int32_t, 4096, 256);
+        else if (table_rows == 8192) GJ_JP(int32_t, 8192, 512);
+        else GJ_JP(int32_t, 16384, 1024);
     } else {
-        if (table_rows == 4096) GJ_JP(int64_t, 4096);
-        else GJ_JP(int64_t, 8192);
+        if (table_rows == 4096 && waves == 16) GJ_JP(int64_t, 4096, 1024);
+        else if (table_rows == 4096) GJ_JP(int64_t, 4096, 256);
+        else GJ_JP(int64_t, 8192, 512);
     }
 #undef GJ_JP
 }
 
-uint32_t waves_per_unit(uint32_t table_rows) { return table_rows / 16 / kWave; }
+// Waves of a unit: one for 1024 table rows; 16 for 4096-row tables where an eager
+// join has at most two units per compute unit, so that four waves each leave most
+// of the chip idle, and on average four S rows for each of the 1024 threads.
+// 2^16 x 2^20 rows: count 19 -> 12 us, write 28 -> 16 us, the call 149 -> 137; 322061
+// x 1.4M rows: kernels 41 -> 27 us, the call the same. Past either bound the call
+// does not gain: with fewer S rows per unit (322061 x 364065) 149 us against 152
+// although the kernels take 32 -> 27; with more units the count pass loses (2^21
+// x 2^24 rows: 50 against 60 us) what the write pass gains (156 against 145).
+constexpr uint64_t kFewUnits = 512;
+uint32_t waves_per_unit(uint32_t table_rows, uint64_t units, uint64_t s_rows) {
+    return table_rows == 4096 && units <= kFewUnits && s_rows >= units * 4096 ? 16u : table_rows / 1024u;
+}
 
 // Largest LDS the staged streaming pass may take (GJ_JOIN_STAGED_LDS overrides;
 // 0 turns the staged pass off).
@@ -1203,7 +1229,6 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
     require(r_block >= 64 && r_block <= join_max_r_block(key_bytes),
             key_bytes == 4 ? "R build block must be 64..16384 rows" : "R build block must be 64..8192 rows for 8-byte keys");
     const uint32_t table_rows = join_table_rows(r_block);
-    const uint32_t wpu = waves_per_unit(table_rows);
     const uint32_t np = seg_bits ? (n_inst << 8) : (1u << bits);
     uint32_t *ucnt = ctx.scratch_n<uint32_t>(np + 1);
     uint32_t *flags = ctx.scratch_n<uint32_t>(6);  // [0..3] flags, [4..5] 64-bit unit total
@@ -1211,6 +1236,7 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
     // Units of a single join whose partitions have one R block each.
     const uint64_t bound = (uint64_t)np + ceil_div_u32(S.rows, join_s_piece(r_block));
     const bool one_kernel = !pl && !seg_bits && bound <= kOneKernelUnits;
+    const uint32_t wpu = one_kernel ? waves_per_unit(table_rows, bound, S.rows) : table_rows / 1024u;
     // Single joins with 4096-row tables do not wait for the unit count: the count
     // pass runs for the bound, with LDS for R blocks a quarter over the mean
     // partition, and the one read that sizes the output tells whether both held
@@ -1302,7 +1328,7 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
         wcnt = ctx.scratch_n<uint64_t>(nw + 1);
         total = pl ? pl->total : wcnt + nw;
         a.wcnt = wcnt;
-        launch_join_pass(0, key_bytes, table_rows, s, pl != nullptr, grid, a, key_reads);
+        launch_join_pass(0, key_bytes, table_rows, wpu, s, pl != nullptr, grid, a, key_reads);
         if (pl || guess) scan_exclusive_u64_dev(ctx, wcnt, wcnt, nw, nunits, wpu, total);
         else scan_exclusive_u64(ctx, wcnt, wcnt, nw, total);
         if (pl) {
@@ -1381,11 +1407,11 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
     }
     // Eager calls launch the one write pass the count pass chose; plans launch
     // both, and the one that does not apply returns at once.
-    if (shm) launch_join_pass(3, key_bytes, table_rows, s, false, grid, a, sbytes, shm);
-    else if (pl || !complex) launch_join_pass(1, key_bytes, table_rows, s, pl != nullptr, grid, a, sbytes);
+    if (shm) launch_join_pass(3, key_bytes, table_rows, wpu, s, false, grid, a, sbytes, shm);
+    else if (pl || !complex) launch_join_pass(1, key_bytes, table_rows, wpu, s, pl != nullptr, grid, a, sbytes);
     if (pl || complex) {
         const double lbytes = pl ? 0.0 : wbytes;  // a plan counts its bytes once, on the streaming pass
-        launch_join_pass(2, key_bytes, table_rows, s, pl != nullptr, grid, a, lbytes, dups && !gfur ? 1 : 0);
+        launch_join_pass(2, key_bytes, table_rows, wpu, s, pl != nullptr, grid, a, lbytes, dups && !gfur ? 1 : 0);
     }
     return pl ? 0 : (int64_t)T;
 }

@@ -83,3 +83,26 @@ def test_uneven_partitions(big, mat):
     else:
         for a, b in zip(canon(got), canon(want)):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("key64", [False, True])
+@pytest.mark.parametrize("n_s", [131071, 131072, 496 * 8192, 496 * 8192 + 1])
+def test_units_of_few_and_many_waves(n_s, key64):
+    """16 partitions: units of 16 waves from 131072 S rows (4096 for each of 32 units)
+    to 496 S pieces (512 units), of four on either side; some S rows match nothing,
+    some R keys repeat."""
+    import paper_2312_00720_amd as gj
+    from gpu_util import dev, host, say
+    say(f"join waves n_s={n_s} key64={key64}")
+    g = datagen.rng(n_s + key64)
+    dt = np.int64 if key64 else np.int32
+    rk = g.permutation(np.concatenate([np.arange(18000), np.arange(2000)])).astype(dt)
+    sk = g.integers(0, 24000, size=n_s).astype(dt)
+    rp, sp = datagen.payload_columns(g, len(rk), 1), datagen.payload_columns(g, n_s, 1)
+    k, r, s = gj.join(dev(rk), [dev(x) for x in rp], dev(sk), [dev(x) for x in sp], mat="gftr", algo="phj")
+    got = [host(k)] + [host(x) for x in r + s]
+    want = oracle.join(rk, rp, sk, sp)
+    assert len(got[0]) == len(want[0])
+    order = np.argsort(want[0] & 15, kind="stable")
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(a, np.asarray(b)[order])
