@@ -2777,6 +2777,10 @@ int64_t groupby_hash(Ctx &ctx, int key_bytes, const void *key, const ValCols &vc
         const uint32_t per_cu = (uint32_t)std::max<size_t>(1, std::min<size_t>(wide ? 2 : 8, max_lds / alds));
         // about two rounds of resident workgroups over all slices, chunks a multiple of the XCDs
         uint32_t chunks = ceil_div_u32(2u * 256u * per_cu, slices);
+        // No chunk below one round of rows of its workgroup: every workgroup sets up and
+        // flushes all records of its slice (10007 rows, 100 groups: 99 us with 4096
+        // chunks, 12 with 8).
+        chunks = std::min(chunks, ceil_div_u32(n, (wide ? 1024u : kBlock) * (nvt <= 2 ? 8u : 16u / nvt)));
         chunks = std::max<uint32_t>(kXcds, (chunks + kXcds - 1) / kXcds * kXcds);
         a.chunks = chunks;
         a.chunk_rows = ceil_div_u32(n, chunks);
