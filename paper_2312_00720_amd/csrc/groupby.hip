@@ -1506,9 +1506,8 @@ __device__ __forceinline__ uint32_t hgb_insert_from(const HgbArgs &a, const K *k
 // home slot. (Reading a round's home slots together first was faster with a
 // few dozen groups but 10-20% slower from 2^14 groups up; the cached kernel
 // below serves the small counts.)
-template <typename K>
+template <typename K, int RB>
 __global__ __launch_bounds__(kBlock) void k_hgb_insert(HgbArgs a) {
-    constexpr int RB = 16;
     const K *__restrict__ keys = static_cast<const K *>(a.keys);
     const uint64_t mask = (1ull << a.log2cap) - 1ull;
     const uint32_t stride = gridDim.x * kBlock * RB;
@@ -1533,8 +1532,12 @@ __global__ __launch_bounds__(kBlock) void k_hgb_insert(HgbArgs a) {
 // workgroup has met before never touches the global table. Rows the cache does
 // not hold go to the global table exactly as in k_hgb_insert and are then
 // entered in the cache; the cache only remembers what the global table
-// answered, so the ids are the same. Entries are key << 32 | gid_loc
-// (gid_loc < 2^31, so no entry equals the empty ~0). Whole rounds move keys and
+// answered, so the ids are the same. It starts with the keys that the prefix put
+// into the global table: left to the first rounds, every workgroup resolves every
+// key by itself (2^26 rows, 1000 groups: both inserts 188 -> 103 us, 2000: 213 ->
+// 104, 64: 106 -> 98; 2^25 rows with 8-byte keys, 1000 groups: 165 -> 86).
+// Entries are key << 32 | gid_loc (gid_loc < 2^31, so no entry equals the empty
+// ~0). Whole rounds move keys and
 // gid_loc as 16-byte runs of 4 rows (both arrays 16-byte aligned).
 constexpr int kInsBlock = 1024;
 constexpr int kInsRows = 8;  // rows per thread and round
@@ -1543,6 +1546,14 @@ constexpr int kCacheProbe = 8;
 template <int LOG2C>
 __device__ __forceinline__ uint32_t cache_home(int32_t k) {
     return ((uint32_t)k * 0x9E3779B1u) >> (32 - LOG2C);
+}
+
+template <int LOG2C>
+__device__ __forceinline__ void cache_enter(unsigned long long *s_c, uint32_t home, unsigned long long ent) {
+    for (int p = 0; p < kCacheProbe; ++p) {
+        const unsigned long long old = atomicCAS(&s_c[(home + p) & ((1u << LOG2C) - 1u)], ~0ull, ent);
+        if (old == ~0ull || (uint32_t)(old >> 32) == (uint32_t)(ent >> 32)) break;
+    }
 }
 
 template <int LOG2C, int RB>
@@ -1582,11 +1593,7 @@ __device__ __forceinline__ void insert_cached_rows(const HgbArgs &a, unsigned lo
     for (int r = 0; r < RB; ++r) {
         if (!((miss >> r) & 1u)) continue;
         loc[r] = hgb_insert_from<int32_t, false>(a, keys, row[r], kk[r], global_slot_hash<int32_t>(kk[r]) & mask);
-        const unsigned long long ent = ((unsigned long long)(uint32_t)kk[r] << 32) | loc[r];
-        for (int p = 0; p < kCacheProbe; ++p) {
-            const unsigned long long old = atomicCAS(&s_c[(ch[r] + p) & CM], ~0ull, ent);
-            if (old == ~0ull || (uint32_t)(old >> 32) == (uint32_t)kk[r]) break;
-        }
+        cache_enter<LOG2C>(s_c, ch[r], ((unsigned long long)(uint32_t)kk[r] << 32) | loc[r]);
     }
 }
 
@@ -1597,6 +1604,16 @@ __global__ __launch_bounds__(kInsBlock, 8) void k_hgb_insert_cached(HgbArgs a) {
     __shared__ unsigned long long s_c[1u << LOG2C];
     for (uint32_t j = threadIdx.x; j < (1u << LOG2C); j += kInsBlock) s_c[j] = ~0ull;
     __syncthreads();
+    // the keys that the prefix found (a filled slot is final; a far larger table, which
+    // the retry without an estimate takes, is left alone)
+    if (a.log2cap <= LOG2C + 1) {
+        const unsigned long long *t = static_cast<const unsigned long long *>(a.table);
+        for (uint32_t j = threadIdx.x; j < (1u << a.log2cap); j += kInsBlock) {
+            const unsigned long long ent = t[j];
+            if (ent != ~0ull) cache_enter<LOG2C>(s_c, cache_home<LOG2C>((int32_t)(ent >> 32)), ent);
+        }
+        __syncthreads();
+    }
     const int32_t *__restrict__ keys = static_cast<const int32_t *>(a.keys);
     const uint32_t stride = gridDim.x * kRound;
     uint32_t base = blockIdx.x * kRound;
@@ -1659,6 +1676,18 @@ __device__ __forceinline__ uint32_t cache_home8(long long k) {
     return ((uint32_t)(u ^ (u >> 32)) * 0x9E3779B1u) >> (32 - LOG2C);
 }
 
+template <int LOG2C>
+__device__ __forceinline__ void cache_enter8(long long *s_k, uint32_t *s_l, uint32_t home, long long k, uint32_t loc) {
+    if (k == kCacheNoKey) return;
+    for (int p = 0; p < kCacheProbe; ++p) {
+        const uint32_t slot = (home + p) & ((1u << LOG2C) - 1u);
+        const long long old = (long long)atomicCAS(reinterpret_cast<unsigned long long *>(&s_k[slot]),
+                                                   (unsigned long long)kCacheNoKey, (unsigned long long)k);
+        if (old == kCacheNoKey) s_l[slot] = loc;
+        if (old == kCacheNoKey || old == k) break;
+    }
+}
+
 template <int LOG2C, int RB>
 __device__ __forceinline__ void insert_cached_rows8(const HgbArgs &a, long long *s_k, uint32_t *s_l,
                                                     const long long (&kk)[RB], const uint32_t (&row)[RB],
@@ -1697,14 +1726,7 @@ __device__ __forceinline__ void insert_cached_rows8(const HgbArgs &a, long long 
     for (int r = 0; r < RB; ++r) {
         if (!((miss >> r) & 1u)) continue;
         loc[r] = hgb_insert_from<long long, false>(a, keys, row[r], kk[r], global_slot_hash<long long>(kk[r]) & mask);
-        if (kk[r] == kCacheNoKey) continue;
-        for (int p = 0; p < kCacheProbe; ++p) {
-            const uint32_t slot = (ch[r] + p) & CM;
-            const long long old = (long long)atomicCAS(reinterpret_cast<unsigned long long *>(&s_k[slot]),
-                                                       (unsigned long long)kCacheNoKey, (unsigned long long)kk[r]);
-            if (old == kCacheNoKey) s_l[slot] = loc[r];
-            if (old == kCacheNoKey || old == kk[r]) break;
-        }
+        cache_enter8<LOG2C>(s_k, s_l, ch[r], kk[r], loc[r]);
     }
 }
 
@@ -1720,6 +1742,17 @@ __global__ __launch_bounds__(kInsBlock, 8) void k_hgb_insert_cached8(HgbArgs a) 
     }
     __syncthreads();
     const long long *__restrict__ keys = static_cast<const long long *>(a.keys);
+    // the keys that the prefix found, as in the kernel for 4-byte keys
+    if (a.log2cap <= LOG2C + 1) {
+        const uint32_t *t = static_cast<const uint32_t *>(a.table);
+        for (uint32_t j = threadIdx.x; j < (1u << a.log2cap); j += kInsBlock) {
+            const uint32_t loc = t[j];
+            if (loc == 0xFFFFFFFFu) continue;
+            const long long k = keys[loc];
+            cache_enter8<LOG2C>(s_k, s_l, cache_home8<LOG2C>(k), k, loc);
+        }
+        __syncthreads();
+    }
     const uint32_t stride = gridDim.x * kRound;
     uint32_t base = blockIdx.x * kRound;
     for (; (uint64_t)base + kRound <= a.n; base += stride) {
@@ -2639,9 +2672,9 @@ void groupby_partition_segments(Ctx &ctx, int key_bytes, const void *key, const 
 // The table: 1.5 slots per row always holds every group; with a group-count
 // estimate it is sized for that instead (load `occupancy`, default 0.45), and a
 // row that finds no slot within 4096 probes sends the insert back to the
-// row-sized table.
+// row-sized table. any_order: ids need not follow the rows.
 static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *key, uint32_t n, uint32_t prefix,
-                        double g_est, float occupancy) {
+                        double g_est, float occupancy, bool any_order) {
     hipStream_t st = ctx.stream;
     a.keys = key;
     a.n = n;
@@ -2650,6 +2683,12 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
     a.gid_loc = ctx.scratch_n<uint32_t>(n);
     a.ngroups = ctx.scratch_n<uint32_t>(2);
     a.tmp_keys = ctx.scratch((size_t)n * key_bytes);
+    // Where the order of the ids does not matter and the cached kernels follow, the
+    // prefix only has to fill the table that they copy: many workgroups, 16 rows per
+    // group. What it misses, every workgroup of the full pass looks up on its own.
+    const bool spread = any_order && g_est > 0.0 && g_est <= (key_bytes == 4 ? 6144.0 : 3072.0);
+    // Up to 2048 rows it takes them all, and there is no full pass to launch.
+    if (spread) prefix = std::max<uint32_t>(n <= 2048 ? 2048u : (uint32_t)kBlock, (uint32_t)(g_est * 16.0));
     prefix = std::min(prefix, n);
     const uint32_t grid = std::min<uint32_t>(ceil_div_u32(n, kBlock), 256u * 16u);
     int log2rows = 4;
@@ -2663,8 +2702,10 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
         fill_u32(st, a.ngroups, 0u, 2);
         HgbArgs ap = a;
         ap.n = prefix;
+        const uint32_t pblocks = spread ? ceil_div_u32(prefix, kBlock) : 1;
         if (key_bytes == 4) {
-            GJ_LAUNCH("k_hgb_insert", 8.0 * prefix, k_hgb_insert<int32_t>, dim3(1), dim3(kBlock), 0, st, ap);
+            GJ_LAUNCH("k_hgb_insert", 8.0 * prefix, (k_hgb_insert<int32_t, 1>), dim3(pblocks), dim3(kBlock), 0,
+                      st, ap);
             if (n > prefix) {
                 // up to a few thousand groups: every workgroup caches the keys it
                 // resolved (an 8192-entry LDS table, at most three quarters full)
@@ -2673,10 +2714,11 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
                               dim3(std::min<uint32_t>(ceil_div_u32(n, kInsBlock * kInsRows), 512)), dim3(kInsBlock), 0, st,
                               a);
                 else
-                    GJ_LAUNCH("k_hgb_insert", 8.0 * n, k_hgb_insert<int32_t>, dim3(grid), dim3(kBlock), 0, st, a);
+                    GJ_LAUNCH("k_hgb_insert", 8.0 * n, (k_hgb_insert<int32_t, 16>), dim3(grid), dim3(kBlock), 0, st, a);
             }
         } else {
-            GJ_LAUNCH("k_hgb_insert", 12.0 * prefix, k_hgb_insert<int64_t>, dim3(1), dim3(kBlock), 0, st, ap);
+            GJ_LAUNCH("k_hgb_insert", 12.0 * prefix, (k_hgb_insert<int64_t, 1>), dim3(pblocks), dim3(kBlock), 0,
+                      st, ap);
             if (n > prefix) {
                 // up to a few thousand groups: a 4096-entry LDS cache per workgroup
                 if (g_est > 0.0 && g_est <= 3072.0 && ((uintptr_t)key & 15u) == 0 && ((uintptr_t)a.gid_loc & 15u) == 0)
@@ -2684,7 +2726,7 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
                               dim3(std::min<uint32_t>(ceil_div_u32(n, kInsBlock * kInsRows8), 512)), dim3(kInsBlock),
                               0, st, a);
                 else
-                    GJ_LAUNCH("k_hgb_insert", 12.0 * n, k_hgb_insert<int64_t>, dim3(grid), dim3(kBlock), 0, st, a);
+                    GJ_LAUNCH("k_hgb_insert", 12.0 * n, (k_hgb_insert<int64_t, 16>), dim3(grid), dim3(kBlock), 0, st, a);
             }
         }
         uint32_t h[2];
@@ -2721,7 +2763,7 @@ int64_t groupby_hash(Ctx &ctx, int key_bytes, const void *key, const ValCols &vc
     const size_t rec_odd = (size_t)make_spec(aggs, n_aggs, no_outs.data(), vc.width, true).words * 4;
     const size_t budget = std::min(lds_budget > 0 ? (size_t)lds_budget : (size_t)64 * 1024, (size_t)64 * 1024);
     const uint32_t prefix = (uint32_t)std::max<size_t>(2048, 2 * (budget / rec_even));
-    const uint32_t g = hgb_assign_ids(ctx, a, key_bytes, key, n, prefix, g_est, occupancy);
+    const uint32_t g = hgb_assign_ids(ctx, a, key_bytes, key, n, prefix, g_est, occupancy, lds_budget <= 0);
     *out_key = ctx.output((size_t)std::max<uint32_t>(g, 1) * key_bytes);
     std::vector<void *> outs(n_aggs);
     for (int j = 0; j < n_aggs; ++j) {
@@ -2917,7 +2959,7 @@ int64_t groupby_sort_de(Ctx &ctx, int key_bytes, const void *key, const ValCols 
     hipStream_t st = ctx.stream;
     // the dictionary: Algorithm 1's dense ids over the distinct keys
     HgbArgs h{};
-    const uint32_t g = hgb_assign_ids(ctx, h, key_bytes, key, n, 2048, g_est, occupancy);
+    const uint32_t g = hgb_assign_ids(ctx, h, key_bytes, key, n, 2048, g_est, occupancy, true);
     *out_key = ctx.output((size_t)std::max<uint32_t>(g, 1) * key_bytes);
     std::vector<void *> outs(n_aggs);
     for (int j = 0; j < n_aggs; ++j) {
