@@ -30,16 +30,16 @@ void check_col(const gj_col &c, int64_t n, const char *what) {
     gj::require(n == 0 || c.data != nullptr, std::string(what) + ": null data");
 }
 
-// Chunk rows of the partition group-by's pass: the key and, unless only row ids
+// Chunks of the partition group-by's pass: the key and, unless only row ids
 // move (gfur), the value columns.
-uint32_t gb_chunk_rows(uint32_t n, int kb, int n_vals, const int *width, bool gfur) {
+gj::PassCounts gb_chunks(uint32_t n, int kb, int n_vals, const int *width, bool gfur) {
     uint32_t row = (uint32_t)kb + (gfur ? 4u : 0u);
     bool narrow = kb == 4;
     for (int i = 0; i < n_vals && !gfur; ++i) {
         row += (uint32_t)width[i];
         narrow = narrow && width[i] == 4;
     }
-    return gj::pass_chunk_rows(n, row, narrow);
+    return gj::pass_chunks(n, row, narrow);
 }
 
 void check_rel(const gj_rel *r, const char *what) {
@@ -436,12 +436,11 @@ int gj_groupby(gj_col key, const gj_col *vals, int32_t n_vals, int64_t n_rows, c
         int varying = 0;
         // a partition group-by (chosen, or possibly chosen) takes its first pass's
         // histogram from the same read of the keys
-        const uint32_t *hist8 = nullptr;
+        gj::PassCounts counts = gb_chunks(n, kb, vcols.n, vcols.width, gfur);
         const bool want_hist = algo == GJ_GB_AUTO || (algo == GJ_GB_PARTITION && o.radix_bits == 0);
-        const uint32_t chunk_rows = gb_chunk_rows(n, kb, vcols.n, vcols.width, gfur);
         if (algo == GJ_GB_AUTO || algo == GJ_GB_HASH || algo == GJ_GB_SORT_DE ||
             (algo == GJ_GB_PARTITION && o.radix_bits == 0))
-            g_est = gj::estimate_groups(ctx, kb, key.data, n, &varying, want_hist ? &hist8 : nullptr, chunk_rows);
+            g_est = gj::estimate_groups(ctx, kb, key.data, n, &varying, want_hist ? &counts : nullptr);
         if (algo == GJ_GB_AUTO) {
             float f[12];
             gj::features_groupby(f, (double)n, kb, n_vals, g_est, varying, o.skew_hint,
@@ -477,7 +476,7 @@ int gj_groupby(gj_col key, const gj_col *vals, int32_t n_vals, int64_t n_rows, c
             }
             int fell_back = 0;
             g = gj::groupby_partition(ctx, kb, key.data, vcols, n, aggs, n_aggs, gfur, bits, &okey, oaggs,
-                                      &fell_back, hist8);
+                                      &fell_back, want_hist ? &counts : nullptr);
             if (fell_back) algo = GJ_GB_HASH;  // too many distinct keys per partition
         }
         if (algo == GJ_GB_HASH)
@@ -552,10 +551,9 @@ int gj_groupby_features(gj_col key, const gj_col *vals, int32_t n_vals, const gj
         // the same sketch kernel gj_groupby runs for these options (with the
         // per-chunk hash histogram for a partition pass, which is dropped here)
         const bool want_hist = o.algo == GJ_GB_AUTO || (o.algo == GJ_GB_PARTITION && o.radix_bits == 0);
-        const uint32_t *hist8 = nullptr;
+        gj::PassCounts counts = gb_chunks((uint32_t)n_rows, kb, n_vals, vw, o.mat == GJ_MAT_GFUR);
         const double g_est =
-            gj::estimate_groups(ctx, kb, key.data, (uint32_t)n_rows, &varying, want_hist ? &hist8 : nullptr,
-                                gb_chunk_rows((uint32_t)n_rows, kb, n_vals, vw, o.mat == GJ_MAT_GFUR));
+            gj::estimate_groups(ctx, kb, key.data, (uint32_t)n_rows, &varying, want_hist ? &counts : nullptr);
         gj::features_groupby(features, (double)n_rows, kb, n_vals, g_est, varying, o.skew_hint,
                              (double)gj::hgb_record_bytes(aggs, n_aggs, vw));
         return GJ_OK;

@@ -2343,9 +2343,8 @@ size_t hgb_record_bytes(const gj_agg *aggs, int n_aggs, const int *val_w) {
 }
 
 double estimate_groups(Ctx &ctx, int key_bytes, const void *key, uint32_t n, int *varying_bytes,
-                       const uint32_t **hist8, uint32_t chunk_rows) {
+                       PassCounts *counts) {
     if (varying_bytes) *varying_bytes = 0;
-    if (hist8) *hist8 = nullptr;
     if (n == 0) return 0.0;
     hipStream_t st = ctx.stream;
     constexpr int m = 1 << kHllBits;
@@ -2353,11 +2352,11 @@ double estimate_groups(Ctx &ctx, int key_bytes, const void *key, uint32_t n, int
     unsigned long long *bits = reinterpret_cast<unsigned long long *>(regs + m);
     fill_u32(st, regs, 0u, m + 2);
     fill_u32(st, regs + m + 2, 0xFFFFFFFFu, 2);
-    if (hist8) {
+    if (counts) {
         // one workgroup per chunk of the partition pass that may follow
-        const uint32_t crows = chunk_rows, chunks = ceil_div_u32(n, crows);
+        const uint32_t crows = counts->chunk_rows, chunks = ceil_div_u32(n, crows);
         uint32_t *h8 = ctx.scratch_n<uint32_t>((size_t)chunks * 256);
-        *hist8 = h8;
+        counts->hist8 = h8;
 #define GJ_HLL(K, BLOCK)                                                                                       \
     GJ_LAUNCH("k_hll", (double)n * sizeof(K), (k_hll<K, true, BLOCK>), dim3(chunks), dim3(BLOCK), 0, st,       \
               static_cast<const K *>(key), n, regs, bits, crows, h8)
@@ -2406,7 +2405,7 @@ static const uint32_t *pgb_unit_map(Ctx &ctx, const uint32_t *ubase, uint32_t np
 
 int64_t groupby_partition(Ctx &ctx, int key_bytes, const void *key, const ValCols &vc,
                           uint32_t n, const gj_agg *aggs, int n_aggs, bool gfur, int bits, void **out_key,
-                          void **out_aggs, int *fell_back, const uint32_t *hist8) {
+                          void **out_aggs, int *fell_back, const PassCounts *counts) {
     hipStream_t st = ctx.stream;
     *fell_back = 0;
     const int passes = bits > 8 ? 2 : 1;
@@ -2426,7 +2425,7 @@ int64_t groupby_partition(Ctx &ctx, int key_bytes, const void *key, const ValCol
     }
     const uint32_t np = 1u << bits;
     uint32_t *poff = ctx.scratch_n<uint32_t>(np + 1);
-    partition_run(ctx, key_bytes, key, pkey, pc, n, 0, bits, passes, kDigitHash, poff, passes == 1 ? hist8 : nullptr);
+    partition_run(ctx, key_bytes, key, pkey, pc, n, 0, bits, passes, kDigitHash, poff, passes == 1 ? counts : nullptr);
 
     // discover: groups per partition, distinct keys in first-occurrence order
     PgbArgs a{};

@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "scatter_rule.hpp"
 
 namespace gj {
 namespace {
@@ -60,7 +61,7 @@ struct PassArgs {
     uint32_t *poff;              // optional: receives the partition boundaries (segment, digit)
     int off_mode;                // OffsetMode
     uint32_t chunk_rows;
-    int cells;  // long chunks (below): cut at multiples of chunk_rows of the whole input
+    bool cells;  // long chunks (below): cut at multiples of chunk_rows of the whole input
     uint32_t *hist;  // [chunks][2^bits], laid out as (segment, digit, chunk)
     uint32_t n_rows; // rows of the output columns; every store is checked against it
     const uint8_t *seg_bits;  // optional: digit bits per segment (<= bits; batches of instances)
@@ -148,7 +149,6 @@ __device__ ChunkLoc locate_chunk(const PassArgs &a, uint32_t c) {
         else hi = mid;
     }
     const uint32_t cb = a.chunk_base[lo];
-    if (a.cells) return cell_chunk(a, (a.seg_off[lo] - a.seg_off[0]) / a.chunk_rows + (c - cb), lo);
     L.seg = lo;
     L.j = c - cb;
     L.m = a.chunk_base[lo + 1] - cb;
@@ -753,15 +753,7 @@ struct LineLds {
     uint8_t *tab;     // digit of every line
     uint32_t *tmp;
 };
-constexpr size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
-constexpr int kLineWaves = 16;
-constexpr uint32_t line_max(uint32_t D, uint32_t A, uint32_t tile) { return (tile + D * (A - 1)) / A + 1; }  // full lines of a tile, and a spare one
-// LDS bytes of a pass: D digits, row_bytes per row (key and columns), w bytes of the widest column.
-constexpr size_t line_lds_bytes(uint32_t D, uint32_t A, uint32_t row_bytes, uint32_t tile, uint32_t w) {
-    return (size_t)line_max(D, A, tile) * A * w + (size_t)D * A * row_bytes + align16((size_t)kLineWaves * D * 2) +
-           align16((size_t)D * 4) + (size_t)D * 16 + align16((size_t)(D + 1) * 2) + align16(line_max(D, A, tile)) +
-           4 * kLineWaves;
-}
+// The bytes that line_lds_bytes counts.
 __device__ __forceinline__ LineLds line_lds(uint8_t *p, uint32_t D, uint32_t A, uint32_t row_bytes, uint32_t tile,
                                             uint32_t w) {
     LineLds S;
@@ -1211,34 +1203,22 @@ Shape pass_shape(uint32_t n, uint32_t nseg) {
     return sh;
 }
 
-// The whole-line kernel's launch for a pass, if its LDS holds the carry and its
-// 16-byte stores may go to every output column: lines of 32 rows (128 bytes of a
-// 4-byte column) before lines of 16, long tiles before short ones.
+// The whole-line kernel's launch for a pass of shape sh (line_shape).
 template <typename K>
-bool launch_lines(dim3 grid, hipStream_t s, PassArgs &a, double bytes) {
-    constexpr size_t kLds = 160 * 1024 - 128;
+void launch_lines(const LineShape &sh, bool narrow, dim3 grid, hipStream_t s, const PassArgs &a, double bytes) {
     const uint32_t D = 1u << a.bits;
-    const bool wide = sizeof(K) == 8 || a.n4 < a.ncols;
-    uintptr_t at = (uintptr_t)a.key_out;
-    for (int c = 0; c < a.ncols; ++c) at |= (uintptr_t)a.col_out[c];
-    if (at & 15u) return false;
-#define GJ_LN(I, A_, W, NS)                                                                                       \
-    do {                                                                                                          \
-        const size_t lds = line_lds_bytes(D, A_, a.row_bytes, 1024u * I, W ? 8 : 4);                              \
-        if (wide == W && (size_t)D * A_ <= 1024u * NS && lds <= kLds) {                                           \
-            GJ_LAUNCH("k_scatter", bytes, (k_scatter_lines<K, I, A_, W, NS>), grid, dim3(1024), lds, s, a);       \
-            return true;                                                                                          \
-        }                                                                                                         \
-    } while (0)
-    if constexpr (sizeof(K) == 4) {
-        GJ_LN(14, 32, false, 4);
-        GJ_LN(14, 16, false, 4);
-        GJ_LN(8, 16, false, 4);
+    const size_t lds = line_lds_bytes(D, (uint32_t)sh.rows, a.row_bytes, 1024u * (uint32_t)sh.items, narrow ? 4 : 8);
+#define GJ_LN(I, A_, W)                                                                                              \
+    if (narrow != W && sh.items == I && sh.rows == A_) {                                                             \
+        GJ_LAUNCH("k_scatter", bytes, (k_scatter_lines<K, I, A_, W, kLineSlots>), grid, dim3(1024), lds, s, a);      \
+        return;                                                                                                      \
     }
-    GJ_LN(8, 32, true, 4);
-    GJ_LN(8, 16, true, 4);
+    if constexpr (sizeof(K) == 4) {
+        GJ_LN(14, 32, false) GJ_LN(14, 16, false) GJ_LN(8, 16, false)
+    }
+    GJ_LN(8, 32, true) GJ_LN(8, 16, true)
 #undef GJ_LN
-    return false;
+    throw Error(GJ_EINVAL, "unknown line shape");
 }
 
 template <typename K>
@@ -1312,19 +1292,6 @@ __global__ __launch_bounds__(256) void k_key_bits(const K *__restrict__ keys, ui
     fold_key_bits<256 / kWave>(o, x, s_bits, acc);
 }
 
-// Whether a pass takes long chunks and the whole-line kernel: once its output
-// outgrows the 256 MB memory-side cache, which until then puts split lines
-// together again. 4-byte data, 20 bytes a row, 7 bits: 2^24 rows 184 -> 165 us,
-// 2^26 rows 761 -> 575, 2^27 rows 1.58 -> 1.12 ms; 5 bits, whose longer runs
-// split fewer lines: 155 -> 170, 591 -> 558 us; 8 bytes a row, 2^24 rows: no gain.
-// With 8-byte keys or columns a tile has half the rows, so its fixed work weighs
-// more: 24 bytes a row, 7 bits, 2^26 rows 852 -> 817 us, 2^27 rows 1.79 -> 1.60 ms.
-// Not with many segments (a batch's instances, mostly shorter than such a chunk).
-bool long_chunks(uint32_t n, uint32_t nseg, uint32_t row_bytes, bool narrow) {
-    if (scatter_shape().group >= 0 || nseg > kRadix) return false;
-    return (uint64_t)n * row_bytes >= (narrow ? 1ull << 29 : 1ull << 31);
-}
-
 // Rows per chunk: long ones, one for each of the 256 compute units (chunks share
 // lines at their ends: 2^27 rows, 7 bits: 1.12 ms with 256 chunks, 1.20 with
 // 1024); else one tile, at most ~4096 chunks.
@@ -1341,15 +1308,24 @@ uint32_t chunk_rows_for(uint32_t n, uint32_t nseg, bool cells) {
 // of them from L2 take about a microsecond, a scan's launch about five.
 constexpr uint64_t kDirectCounts = 16384;
 
+// Long chunks belong to the default shape.
+bool long_chunks_for(uint32_t n, uint32_t nseg, int bits, uint32_t row_bytes, bool narrow, bool aligned) {
+    return scatter_shape().group < 0 && long_chunks(n, nseg, bits, row_bytes, narrow, aligned);
+}
+
+// counts: what an earlier kernel counted per chunk; the pass then takes its chunks.
 template <typename K>
-void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const uint32_t *hist8 = nullptr) {
+void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const PassCounts *counts = nullptr) {
     hipStream_t s = ctx.stream;
     const uint32_t R = 1u << a.bits;
     a.row_bytes = (uint32_t)sizeof(K);
     for (int c = 0; c < a.ncols; ++c) a.row_bytes += (uint32_t)a.col_w[c];
     const bool narrow = sizeof(K) == 4 && a.n4 == a.ncols;
-    a.cells = long_chunks(n, a.nseg, a.row_bytes, narrow) ? 1 : 0;
-    a.chunk_rows = chunk_rows_for(n, a.nseg, a.cells);
+    uintptr_t at = (uintptr_t)a.key_out;
+    for (int c = 0; c < a.ncols; ++c) at |= (uintptr_t)a.col_out[c];
+    const bool aligned = (at & 15u) == 0;
+    a.cells = counts ? counts->cells : long_chunks_for(n, a.nseg, a.bits, a.row_bytes, narrow, aligned);
+    a.chunk_rows = counts ? counts->chunk_rows : chunk_rows_for(n, a.nseg, a.cells);
     a.n_chunks = ceil_div_u32(n, a.chunk_rows);
     const Shape sh = pass_shape(n, a.nseg);
     const uint64_t max_chunks = a.seg_off ? (uint64_t)a.n_chunks + a.nseg : a.n_chunks;
@@ -1373,35 +1349,39 @@ void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const uint32_t *hist8 = nullptr
     const uint64_t hn = max_chunks * R;
     uint32_t *hist = ctx.scratch_n<uint32_t>(hn);
     a.hist = hist;
-    if (hist8) {
+    if (counts) {
         // one segment: chunks 0..m-1, the digit the low bits of the same source
         const uint32_t m = a.n_chunks;
         GJ_LAUNCH("k_fold_hist", 4.0 * m * 256 + 4.0 * m * R, k_fold_hist,
-                  dim3(std::min<uint32_t>(ceil_div_u32(R * m, kBlock), 4096)), dim3(kBlock), 0, s, hist8, m, a.bits,
+                  dim3(std::min<uint32_t>(ceil_div_u32(R * m, kBlock), 4096)), dim3(kBlock), 0, s, counts->hist8, m, a.bits,
                   hist);
     } else {
         if (a.cells)
-            GJ_LAUNCH("k_hist", (double)n * sizeof(K), k_hist_cells<K>, dim3(a.n_chunks), dim3(1024), 0, s, a);
+            GJ_LAUNCH("k_hist_cells", (double)n * sizeof(K), k_hist_cells<K>, dim3(a.n_chunks), dim3(1024), 0, s, a);
         else
             GJ_LAUNCH("k_hist", (double)n * sizeof(K), k_hist<K>, dim3((uint32_t)max_chunks), dim3(kBlock), 0, s, a);
     }
     if (tiled && hn <= kDirectCounts) a.off_mode = kOffDirect;
     else scan_exclusive_u32(ctx, hist, hist, hn, nullptr);
-    if (a.cells && launch_lines<K>(dim3(a.n_chunks), s, a, (double)n * row_bytes)) return;
-    launch_scatter<K>(sh, dim3((uint32_t)max_chunks), s, a, (double)n * row_bytes);
+    const LineShape ls = line_shape(a.bits, a.row_bytes, narrow);
+    if (a.cells && aligned && ls.items) launch_lines<K>(ls, narrow, dim3(a.n_chunks), s, a, (double)n * row_bytes);
+    else launch_scatter<K>(sh, dim3((uint32_t)max_chunks), s, a, (double)n * row_bytes);
 }
 
 }  // namespace
 
 void set_scatter_variant(int v) { g_variant = v; }
 
-uint32_t pass_chunk_rows(uint32_t n, uint32_t row_bytes, bool narrow) {
-    return chunk_rows_for(n, 1, long_chunks(n, 1, row_bytes, narrow));
+PassCounts pass_chunks(uint32_t n, uint32_t row_bytes, bool narrow) {
+    PassCounts c;
+    c.cells = long_chunks_for(n, 1, 8, row_bytes, narrow, true);
+    c.chunk_rows = chunk_rows_for(n, 1, c.cells);
+    return c;
 }
 
 void partition_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, const PartCols &cols,
-                   uint32_t n, int bit_lo, int bits, int passes, int mode, uint32_t *poff, const uint32_t *hist8) {
-    require(!hist8 || (passes == 1 && bit_lo == 0), "a precomputed histogram serves one pass from bit 0");
+                   uint32_t n, int bit_lo, int bits, int passes, int mode, uint32_t *poff, const PassCounts *counts) {
+    require(!counts || (passes == 1 && bit_lo == 0), "a precomputed histogram serves one pass from bit 0");
     require(key_bytes == 4 || key_bytes == 8, "key width must be 4 or 8 bytes");
     require(bits >= 1 && bits <= 16, "partition bits must be 1..16");
     require(passes >= 1 && passes <= 2, "partition passes must be 1 or 2");
@@ -1450,8 +1430,8 @@ void partition_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, c
         const uint64_t np = (uint64_t)nseg << b[p];
         uint32_t *next = last ? poff : ctx.scratch_n<uint32_t>(np + 1);
         a.poff = next;
-        if (key_bytes == 4) run_pass<int32_t>(ctx, a, n, hist8);
-        else run_pass<int64_t>(ctx, a, n, hist8);
+        if (key_bytes == 4) run_pass<int32_t>(ctx, a, n, counts);
+        else run_pass<int64_t>(ctx, a, n, counts);
         seg = next;
         nseg = (uint32_t)np;
         kin = a.key_out;
