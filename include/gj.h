@@ -14,8 +14,10 @@
  *   - Memory: outputs and scratch come from the caller's gj_allocator, called
  *     on the calling thread. Scratch is released through allocator->free
  *     before the call returns, in stream order (the caller's allocator must be
- *     stream-ordered, as a caching device allocator on `stream` is). A NULL
- *     allocator means hipMallocAsync/hipFreeAsync on `stream`.
+ *     stream-ordered, as a caching device allocator on `stream` is). Small
+ *     scratch shares requests of at most 256 KB, none of them larger than
+ *     4 KB or than what the call takes in other blocks. A NULL allocator
+ *     means hipMallocAsync/hipFreeAsync on `stream`.
  *   - Row counts are at most 2^31 - 1 per relation (row identifiers are
  *     32-bit); larger inputs return GJ_EOVERFLOW.
  *   - Calls on different streams may run concurrently; calls that share a

@@ -30,6 +30,13 @@ void check_col(const gj_col &c, int64_t n, const char *what) {
     gj::require(n == 0 || c.data != nullptr, std::string(what) + ": null data");
 }
 
+// Bytes of a relation's transformed copy: the key, and its payloads or (gfur) row ids.
+uint64_t copied_bytes(int64_t rows, int kb, const gj_col *pay, int n_pay, bool gfur) {
+    uint64_t row = (uint64_t)kb + (gfur ? 4u : 0u);
+    for (int i = 0; i < n_pay && !gfur; ++i) row += (uint64_t)dtype_bytes(pay[i].dtype);
+    return (uint64_t)rows * row;
+}
+
 // Chunks of the partition group-by's pass: the key and, unless only row ids
 // move (gfur), the value columns.
 gj::PassCounts gb_chunks(uint32_t n, int kb, int n_vals, const int *width, bool gfur) {
@@ -160,6 +167,8 @@ int gj_join(const gj_rel *R, const gj_rel *S, const gj_join_opts *opts, const gj
         gj::Ctx ctx(alloc, (hipStream_t)stream);
         gj::JoinSide side[2];
         const gj_rel *rel[2] = {R, S};
+        ctx.expect(copied_bytes(R->n_rows, kb, R->payloads, R->n_payloads, gfur) +
+                   copied_bytes(S->n_rows, kb, S->payloads, S->n_payloads, gfur));
         if (o.algo == GJ_JOIN_SMJ) {
             // transformation: full-key LSD radix sort of (key, payloads) or (key, row id)
             for (int t = 0; t < 2; ++t) {
@@ -323,6 +332,8 @@ int gj_join_batch(const gj_rel_batch *R, const gj_rel_batch *S, const gj_join_op
             soff[i] = (uint32_t)S->offsets[i];
         }
         gj::Ctx ctx(alloc, (hipStream_t)stream);
+        ctx.expect(copied_bytes(nr, kb, R->payloads, R->n_payloads, gfur) +
+                   copied_bytes(ns, kb, S->payloads, S->n_payloads, gfur));
         hipStream_t st = (hipStream_t)stream;
         uint8_t *d_bits = static_cast<uint8_t *>(ctx.scratch(n));
         uint32_t *d_off[2] = {ctx.scratch_n<uint32_t>(n + 1), ctx.scratch_n<uint32_t>(n + 1)};
@@ -431,6 +442,7 @@ int gj_groupby(gj_col key, const gj_col *vals, int32_t n_vals, int64_t n_rows, c
         }
 
         gj::Ctx ctx(alloc, (hipStream_t)stream);
+        ctx.expect((uint64_t)n * kb);  // every algorithm holds the keys once more
         // the group count decides the algorithm and the partition passes: estimate it
         double g_est = 0.0;
         int varying = 0;

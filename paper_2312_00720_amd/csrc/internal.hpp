@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <initializer_list>
 #include <stdexcept>
 #include <string>
@@ -91,14 +92,20 @@ class Ctx {
         if (!committed_)
             for (void *p : outputs_) release(p);
     }
-    // Small requests share blocks of kSlab bytes: a call makes a dozen or two of
-    // them, and each request to the caller's allocator costs more than a
-    // microsecond (through the Python binding).
+    // What the call takes from its allocator for certain (partitioned copies, say).
+    void expect(uint64_t bytes) { sure_ = bytes; }
+    // Small requests share a block: a call makes a dozen or two of them, and each
+    // request to the caller's allocator costs more than a microsecond (through the
+    // Python binding). No such block exceeds what the call takes anyway: its
+    // certain bytes, or a quarter of what it was given so far (a caller's allocator
+    // may have room for little more). Memory of our own pool comes in blocks of kSlab.
     void *scratch(size_t bytes) {
         if (bytes <= kSlabMost && !arena_) {
             const size_t need = bytes == 0 ? 256 : (bytes + 255) & ~size_t(255);
-            if (!slab_ || slab_used_ + need > kSlab) {
-                slab_ = static_cast<char *>(get(kSlab));
+            if (!slab_ || slab_used_ + need > slab_size_) {
+                const size_t least = alloc_ && alloc_->alloc ? (size_t)std::max<uint64_t>({need, kSlabLeast, sure_, asked_ / 4}) : kSlab;
+                slab_size_ = std::min(least, kSlab);
+                slab_ = static_cast<char *>(get(slab_size_));
                 scratch_.push_back(slab_);
                 slab_used_ = 0;
             }
@@ -125,6 +132,7 @@ class Ctx {
     void *get(size_t bytes) {
         if (bytes == 0) bytes = 256;
         bytes = (bytes + 255) & ~size_t(255);
+        asked_ += bytes;
         if (arena_) {
             const size_t off = arena_->used;
             arena_->used += bytes;
@@ -150,9 +158,10 @@ class Ctx {
             (void)hipFreeAsync(p, stream);
         }
     }
-    static constexpr size_t kSlab = 256 * 1024, kSlabMost = 32 * 1024;
+    static constexpr size_t kSlab = 256 * 1024, kSlabMost = 32 * 1024, kSlabLeast = 4096;
     char *slab_ = nullptr;
-    size_t slab_used_ = 0;
+    size_t slab_size_ = 0, slab_used_ = 0;
+    uint64_t sure_ = 0, asked_ = 0;
     std::vector<void *> scratch_, outputs_;
     bool committed_ = false;
     Arena *arena_ = nullptr;
