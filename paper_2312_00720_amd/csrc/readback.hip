@@ -4,10 +4,13 @@
 // one small kernel writes all of them into pinned host memory, and the stream is
 // waited for once.
 //
-// The pinned block belongs to the calling thread: 64 KB, allocated on its first
-// read, given back when the thread ends. Every use ends with the wait, so the
-// thread's next call, on whatever stream, finds it free.
+// A read takes one of the process's pinned blocks and gives it back after the wait, so
+// blocks are only ever shared by reads that follow each other. At most kKeep idle
+// ones are held, until the process ends; no thread frees one at its end, where that
+// would wait for all work on the device.
 #include <string.h>
+
+#include <mutex>
 
 #include "internal.hpp"
 
@@ -15,24 +18,47 @@ namespace gj {
 namespace {
 
 constexpr size_t kPinnedBytes = 65536;
+constexpr size_t kKeep = 16;
 
-struct Pinned {
-    void *p = nullptr;
-    ~Pinned() {
-        if (p) (void)hipHostFree(p);
+class PinnedBlocks {
+  public:
+    ~PinnedBlocks() {
+        for (void *p : idle_) (void)hipHostFree(p);
     }
-    void *get() {
-        if (!p) {
-            hipError_t e = hipHostMalloc(&p, kPinnedBytes, hipHostMallocPortable | hipHostMallocMapped);
-            if (e != hipSuccess) {
-                p = nullptr;
-                throw Error(GJ_EHIP, std::string("pinned host memory: ") + hipGetErrorString(e));
+    void *take() {  // nullptr: none to be had
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            if (!idle_.empty()) {
+                void *p = idle_.back();
+                idle_.pop_back();
+                return p;
             }
         }
-        return p;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, kPinnedBytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return nullptr;
     }
+    void give(void *p) {
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            if (idle_.size() < kKeep) {
+                idle_.push_back(p);
+                return;
+            }
+        }
+        (void)hipHostFree(p);
+    }
+
+  private:
+    std::mutex mu_;
+    std::vector<void *> idle_;
 };
-thread_local Pinned t_pinned;
+
+PinnedBlocks &pinned_blocks() {
+    static PinnedBlocks b;
+    return b;
+}
 
 constexpr int kParts = 4;
 struct ExportArgs {
@@ -54,30 +80,35 @@ __global__ __launch_bounds__(256) void k_export(ExportArgs a) {
 
 void read_back_parts(hipStream_t s, std::initializer_list<ReadPart> parts) {
     size_t total = 0;
-    for (const ReadPart &p : parts) total += p.bytes;
-    if (parts.size() > kParts || total > kPinnedBytes) {
+    for (const ReadPart &p : parts) {
+        require(p.bytes % 4 == 0, "read back whole words", GJ_EHIP);
+        total += p.bytes;
+    }
+    void *host = parts.size() <= (size_t)kParts && total <= kPinnedBytes ? pinned_blocks().take() : nullptr;
+    if (!host) {
         for (const ReadPart &p : parts) GJ_HIP(hipMemcpyAsync(p.host, p.dev, p.bytes, hipMemcpyDeviceToHost, s));
         GJ_HIP(hipStreamSynchronize(s));
         return;
     }
-    char *host = static_cast<char *>(t_pinned.get());
     ExportArgs a{};
     int k = 0;
     for (const ReadPart &p : parts) {
-        require(p.bytes % 4 == 0, "read back whole words", GJ_EHIP);
         a.src[k] = static_cast<const uint32_t *>(p.dev);
         a.words[k++] = (uint32_t)(p.bytes / 4);
     }
     void *dev = nullptr;
+    // on an error from here on the block is not given back: the kernel may still write to it
     GJ_HIP(hipHostGetDevicePointer(&dev, host, 0));
     a.dst = static_cast<uint32_t *>(dev);
     hipLaunchKernelGGL(k_export, dim3(1), dim3(256), 0, s, a);
     GJ_LAUNCHED("k_export");
     GJ_HIP(hipStreamSynchronize(s));
+    const char *from = static_cast<const char *>(host);
     for (const ReadPart &p : parts) {
-        memcpy(p.host, host, p.bytes);
-        host += p.bytes;
+        if (p.bytes) memcpy(p.host, from, p.bytes);
+        from += p.bytes;
     }
+    pinned_blocks().give(host);
 }
 
 }  // namespace gj
