@@ -94,6 +94,7 @@ struct gj_plan {
     hipGraphExec_t exec = nullptr;
     int64_t launches = 0, output_bytes = 0, cap_units_total = 0;
 
+    int device = -1;  // current when the plan was made
     int n = 0, kb = 4, r_block = 4096, variant = 0;
     bool gfur = false;
     const void *rkey = nullptr, *skey = nullptr;
@@ -559,6 +560,25 @@ void build_groupby_plan(gj_plan *P, const gj_gb_batch *B, const gj_agg *aggs, in
 
 int plan_error(int code, const std::string &msg) { return gj::fail(code, msg); }
 
+// Words of a plan's last run to the host. The run may have been enqueued on another
+// stream than the one the caller names: that one is waited for, and the read goes
+// through the default stream of the plan's device, behind work of that stream and of
+// every stream that synchronizes with it.
+void read_plan(gj_plan *P, hipStream_t st, std::initializer_list<gj::ReadPart> parts) {
+    if (st) GJ_HIP(hipStreamSynchronize(st));
+    struct OnDevice {
+        int before = -1;
+        bool moved = false;
+        explicit OnDevice(int d) {
+            if (d >= 0 && hipGetDevice(&before) == hipSuccess && before != d) moved = hipSetDevice(d) == hipSuccess;
+        }
+        ~OnDevice() {
+            if (moved) (void)hipSetDevice(before);
+        }
+    } scope(P->device);
+    gj::read_back_parts(nullptr, parts);
+}
+
 float median(std::vector<float> v) {
     std::sort(v.begin(), v.end());
     return v.empty() ? 0.f : v[v.size() / 2];
@@ -575,6 +595,7 @@ int gj_join_plan_create(const gj_rel_batch *R, const gj_rel_batch *S, const gj_j
     if (!plan) return plan_error(GJ_EINVAL, "null plan pointer");
     *plan = nullptr;
     gj_plan *P = new gj_plan();
+    (void)hipGetDevice(&P->device);
     if (alloc && alloc->alloc) {
         P->alloc = *alloc;
         P->has_alloc = true;
@@ -600,6 +621,7 @@ int gj_groupby_plan_create(const gj_gb_batch *B, const gj_agg *aggs, int32_t n_a
     if (!plan) return plan_error(GJ_EINVAL, "null plan pointer");
     *plan = nullptr;
     gj_plan *P = new gj_plan();
+    (void)hipGetDevice(&P->device);
     if (alloc && alloc->alloc) {
         P->alloc = *alloc;
         P->has_alloc = true;
@@ -627,9 +649,9 @@ int gj_groupby_plan_result(gj_plan *P, void *stream, gj_groupby_out *out, int64_
         const int ng = (int)P->groups.size();
         std::vector<uint64_t> base(ng + 1), off(group_offsets ? P->n + 1 : 0);
         std::vector<uint32_t> status(2 * ng);
-        gj::read_back_parts((hipStream_t)stream, {{base.data(), P->d_base, 8ull * (ng + 1)},
-                                                  {status.data(), P->d_gstatus, 8ull * ng},
-                                                  {off.data(), P->d_inst_off, 8 * off.size()}});
+        read_plan(P, (hipStream_t)stream, {{base.data(), P->d_base, 8ull * (ng + 1)},
+                                           {status.data(), P->d_gstatus, 8ull * ng},
+                                           {off.data(), P->d_inst_off, 8 * off.size()}});
         for (size_t i = 0; i < off.size(); ++i) group_offsets[i] = (int64_t)off[i];
         out->n_groups = (int64_t)base[ng];
         out->key = P->out_key;
@@ -700,13 +722,12 @@ int gj_join_plan_result(gj_plan *P, void *stream, gj_join_out *out, int64_t *out
     if (!P || !out) return plan_error(GJ_EINVAL, "null argument");
     if (P->kind != 0) return plan_error(GJ_EINVAL, "not a join plan");
     try {
-        hipStream_t st = (hipStream_t)stream;
         const int ng = (int)P->groups.size();
         std::vector<uint64_t> base(ng + 1), off(out_offsets ? P->n + 1 : 0);
         std::vector<uint32_t> units(ng);
-        gj::read_back_parts(st, {{base.data(), P->d_base, 8ull * (ng + 1)},
-                                 {units.data(), P->d_units, 4ull * ng},
-                                 {off.data(), P->d_inst_off, 8 * off.size()}});
+        read_plan(P, (hipStream_t)stream, {{base.data(), P->d_base, 8ull * (ng + 1)},
+                                           {units.data(), P->d_units, 4ull * ng},
+                                           {off.data(), P->d_inst_off, 8 * off.size()}});
         for (size_t i = 0; i < off.size(); ++i) out_offsets[i] = (int64_t)off[i];
         const uint64_t T = base[ng];
         out->n_rows = (int64_t)T;
