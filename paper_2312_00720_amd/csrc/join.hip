@@ -24,6 +24,7 @@
 // S row with several matches emits them in R's input order, and the output is
 // the same on every run.
 #include "internal.hpp"
+#include "join_rule.hpp"
 
 namespace gj {
 namespace {
@@ -99,6 +100,8 @@ struct JoinArgs {
     int lds_if_complex;         // LDS write pass: do nothing unless a flag is set (plans)
     uint32_t rlds_off[8];       // staged passes: byte offset of R column j in LDS
     int rstaged;                // LDS write pass: R columns 0..rstaged-1 have a place there
+    uint8_t *wmulti;            // per (unit, wave): lanes with an S row of several matches (count pass)
+    const uint64_t *total;      // output rows of all units
 };
 
 // LDS an eager LDS write pass may use for its table and staged R payloads.
@@ -335,7 +338,7 @@ struct JoinLds {
     uint16_t *b;     // bucket boundaries
     uint32_t *tmp;   // kWv words
     uint32_t *unit;  // 6 words
-    int *is_long;
+    int *is_long;    // a bucket is too long to sort; then: some wave writes in output order
 };
 constexpr size_t align8(size_t x) { return (x + 7) & ~(size_t)7; }
 template <typename K, uint32_t BUILD, int NT>
@@ -523,10 +526,14 @@ __device__ __forceinline__ void count_unit(const JoinArgs &a, uint32_t u, const 
         }
     }
     const uint64_t tot = wave_sum<uint64_t>((uint64_t)cnt);
-    if (lane == 0) a.wcnt[(uint64_t)u * kWv + w] = tot;
+    const uint64_t many = __ballot(multi);
+    if (lane == 0) {
+        a.wcnt[(uint64_t)u * kWv + w] = tot;
+        a.wmulti[(uint64_t)u * kWv + w] = (uint8_t)__popcll(many);
+    }
     // one flag for every wave of the pass: an atomic only while it is not set yet
     // (2^24 x 2^24 rows with duplicate keys, 33 thousand waves: 396 -> 89 us)
-    if (a.flags && __ballot(multi) && lane == 0 &&
+    if (a.flags && many && lane == 0 &&
         !__hip_atomic_load(&a.flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
         atomicOr(&a.flags[1], 1u);
 }
@@ -569,8 +576,8 @@ __device__ __forceinline__ void emit_cols(int j0, int ncols, const void *const *
 // the R payloads in LDS. The waves wait for S payloads and for each other between
 // build and probe; LDS and vector units are a quarter busy.)
 template <typename K>
-__device__ __forceinline__ void write_dups(const JoinArgs &a, const JoinLds<K> &sh, const uint8_t *s_pay, uint32_t r0,
-                                           uint32_t s0, uint32_t ws, uint32_t we, int skip_bits, int log2nb,
+__device__ __forceinline__ void write_dups(const JoinArgs &a, const JoinLds<K> &sh, const uint8_t *s_pay, int staged,
+                                           uint32_t r0, uint32_t s0, uint32_t ws, uint32_t we, int skip_bits, int log2nb,
                                            uint64_t outpos) {
     constexpr int U = 4;
     const int lane = lane_id();
@@ -625,7 +632,7 @@ __device__ __forceinline__ void write_dups(const JoinArgs &a, const JoinLds<K> &
             for (int u = 0; u < U; ++u)
                 if (u * kWave < n) tkey[p + u * kWave] = kv[u];
             emit_cols<U>(0, a.ns, a.sp, a.sw, a.ts, srow, p, n);
-            for (int j = 0; j < a.rstaged; ++j) {
+            for (int j = 0; j < staged; ++j) {
                 uint32_t lrow[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) lrow[u] = rrow[u] - r0;
@@ -643,7 +650,7 @@ __device__ __forceinline__ void write_dups(const JoinArgs &a, const JoinLds<K> &
                         if (u * kWave < n) out[u * kWave] = col[lrow[u]];
                 }
             }
-            emit_cols<U>(a.rstaged, a.nr, a.rp, a.rw, a.tr, rrow, p, n);
+            emit_cols<U>(staged, a.nr, a.rp, a.rw, a.tr, rrow, p, n);
         }
         outpos += t;
     }
@@ -663,11 +670,12 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
     uint16_t *s_b = sh.b;
     uint16_t *s_entry = sh.entry;
     uint32_t *s_unit = sh.unit;
-    int &s_long = *sh.is_long;
+    int &s_long = sh.is_long[0], &s_in_order = sh.is_long[1];
     const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
     if (tid == 0) {
         decode_unit<kSPiece>(a, u, s_unit);
         s_long = 0;
+        s_in_order = 0;
     }
     __syncthreads();
     const uint32_t r0 = s_unit[0], rn = s_unit[1], s0 = s_unit[2], sn = s_unit[3];
@@ -676,6 +684,17 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
     while ((1u << log2nb) < rn) ++log2nb;
     log2nb = min(log2nb + (int)s_unit[5], G::kMaxLog2nb);
     const uint32_t nb = 1u << log2nb;
+    // each wave's share of the S piece, and how it writes its matches
+    const uint32_t q = ceil_div_u32(sn, kWv);
+    const uint32_t ws = min(sn, w * q), we = min(sn, ws + q);
+    const bool dups = a.flags[1] != 0;
+    bool in_order = false;
+    if (dups) {
+        const uint64_t at = (uint64_t)u * kWv + w, slots = (uint64_t)units_to_run(a.nunits, a.flags, a.cap_units) * kWv;
+        const uint64_t out = (at + 1 < slots ? a.woff[at + 1] : *a.total) - a.woff[at];
+        in_order = __builtin_amdgcn_readfirstlane(write_in_order(a.nr + a.ns, a.wmulti[at], out, we - ws));
+        if (in_order && lane == 0) s_in_order = 1;
+    }
 
     // ---- build: bucket counts, scan, placement, per-bucket order by row ----
     const K *__restrict__ rkey = static_cast<const K *>(a.rkey);
@@ -694,7 +713,6 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
     __syncthreads();
     // chains in row order, so that every S row emits its matches in R's input
     // order; where S rows match several R rows, in (key, row) order
-    const bool dups = a.flags[1] != 0;
     for (uint32_t b = tid; b < nb; b += kBlockT) {
         const uint32_t lo = s_b[b], hi = s_b[b + 1];
         if (hi - lo > kMaxChainSort) {
@@ -761,14 +779,15 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
     // ---- probe: each wave streams a contiguous share of the S piece, PB
     // rounds of 64 rows at a time so that many loads are in flight ----
     const K *__restrict__ skey = static_cast<const K *>(a.skey);
-    const uint32_t q = ceil_div_u32(sn, kWv);
-    const uint32_t ws = min(sn, w * q), we = min(sn, ws + q);
-    if (dups && !s_long) {
+    in_order = in_order && !s_long;
+    uint8_t *s_pay = reinterpret_cast<uint8_t *>(sh.is_long) + 8;
+    int staged = 0;
+    if (s_in_order && !s_long) {
         // R payloads that fit beside the table: read once, in order, into LDS (each
         // is used by several output rows, and their gathers were what the waves
         // waited for)
-        uint8_t *s_pay = reinterpret_cast<uint8_t *>(sh.is_long) + 8;
-        for (int j = 0; j < a.rstaged; ++j) {
+        staged = a.rstaged;
+        for (int j = 0; j < staged; ++j) {
             if (a.rw[j] == 4) {
                 const uint32_t *__restrict__ in = static_cast<const uint32_t *>(a.rp[j]) + r0;
                 uint32_t *d = reinterpret_cast<uint32_t *>(s_pay + a.rlds_off[j]);
@@ -780,7 +799,9 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
             }
         }
         __syncthreads();
-        write_dups<K>(a, sh, s_pay, r0, s0, ws, we, skip_bits, log2nb, out_base + a.woff[(uint64_t)u * kWv + w]);
+    }
+    if (in_order) {
+        write_dups<K>(a, sh, s_pay, staged, r0, s0, ws, we, skip_bits, log2nb, out_base + a.woff[(uint64_t)u * kWv + w]);
     } else {
         uint64_t outpos = out_base + a.woff[(uint64_t)u * kWv + w];
         K *__restrict__ tkey = static_cast<K *>(a.tkey);
@@ -1328,6 +1349,8 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
         wcnt = ctx.scratch_n<uint64_t>(nw + 1);
         total = pl ? pl->total : wcnt + nw;
         a.wcnt = wcnt;
+        a.wmulti = ctx.scratch_n<uint8_t>(nw);
+        a.total = total;
         launch_join_pass(0, key_bytes, table_rows, wpu, s, pl != nullptr, grid, a, key_reads);
         if (pl || guess) scan_exclusive_u64_dev(ctx, wcnt, wcnt, nw, nunits, wpu, total);
         else scan_exclusive_u64(ctx, wcnt, wcnt, nw, total);
