@@ -104,9 +104,6 @@ struct JoinArgs {
     const uint64_t *total;      // output rows of all units
 };
 
-// LDS an eager LDS write pass may use for its table and staged R payloads.
-constexpr size_t kJoinWriteLds = 156 * 1024;
-
 // Most work units one call may have: unit indices and their scanned offsets
 // are 32-bit.
 constexpr uint64_t kMaxUnits = 0x7FFFFFFFull;
@@ -1169,19 +1166,19 @@ struct JoinKernels {
     static void staged(hipStream_t s, uint32_t grid, size_t shm, const JoinArgs &a, double bytes) {
         GJ_LAUNCH("k_join_write", bytes, (k_join_stream_staged<K, BUILD, NT>), dim3(grid), dim3(G::kThreads), shm, s, a);
     }
-    // R payload columns beside the table, as many as fit (S rows with several matches)
+    // R payload columns beside the table, as many as leave waves enough (S rows with several matches)
     static size_t stage_r(JoinArgs &a) {
         size_t shm = join_lds_bytes<K, BUILD, NT>(a.lds_rows), used = 0;
         for (; a.rstaged < a.nr; ++a.rstaged) {
             const size_t b = ((size_t)a.lds_rows * a.rw[a.rstaged] + 15) & ~(size_t)15;
-            if (shm + used + b > kJoinWriteLds) break;
+            if (!staging_fits(shm + used + b, G::kWv)) break;
             a.rlds_off[a.rstaged] = (uint32_t)used;
             used += b;
         }
         return shm + used;
     }
-    static void write_lds(hipStream_t s, bool planned, uint32_t grid, JoinArgs a, double bytes, bool dups) {
-        const size_t shm = dups ? stage_r(a) : join_lds_bytes<K, BUILD, NT>(a.lds_rows);
+    static void write_lds(hipStream_t s, bool planned, uint32_t grid, JoinArgs a, double bytes, bool stage) {
+        const size_t shm = stage ? stage_r(a) : join_lds_bytes<K, BUILD, NT>(a.lds_rows);
         if constexpr (G::kRows == 16) {
             if (planned) {
                 GJ_LAUNCH("k_join_write_lds", bytes, (k_join_persist<K, BUILD, NT, true>), dim3(grid), dim3(G::kThreads), shm, s, a);
@@ -1194,7 +1191,7 @@ struct JoinKernels {
 
 // Pass 0 = count, 1 = streaming write, 2 = LDS write, 3 = streaming write with
 // the R side staged in shm bytes of LDS; the table shape holds r_block rows. Pass 2
-// with shm != 0: S rows match several R rows, R payloads may be staged.
+// with shm != 0: R payloads may be staged.
 // waves: of a unit (waves_per_unit).
 void launch_join_pass(int pass, int key_bytes, uint32_t table_rows, uint32_t waves, hipStream_t s, bool planned,
                       uint32_t grid, const JoinArgs &a, double bytes, size_t shm = 0) {
@@ -1434,7 +1431,8 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
     else if (pl || !complex) launch_join_pass(1, key_bytes, table_rows, wpu, s, pl != nullptr, grid, a, sbytes);
     if (pl || complex) {
         const double lbytes = pl ? 0.0 : wbytes;  // a plan counts its bytes once, on the streaming pass
-        launch_join_pass(2, key_bytes, table_rows, wpu, s, pl != nullptr, grid, a, lbytes, dups && !gfur ? 1 : 0);
+        launch_join_pass(2, key_bytes, table_rows, wpu, s, pl != nullptr, grid, a, lbytes,
+                         dups && !gfur && stage_payloads(a.nr + a.ns, T, S.rows) ? 1 : 0);
     }
     return pl ? 0 : (int64_t)T;
 }

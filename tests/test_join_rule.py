@@ -1,5 +1,6 @@
-"""The rule by which a wave of a join's LDS write pass emits its matches
-(csrc/join_rule.hpp), compiled for the host: the faster side where both were timed."""
+"""The rule by which a wave of a join's LDS write pass emits its matches, and by
+which R payloads get room in LDS (csrc/join_rule.hpp), compiled for the host: the faster
+side where both were timed, and the waves a compute unit keeps."""
 import ctypes
 import os
 import subprocess
@@ -14,6 +15,10 @@ SRC = """
 extern "C" int in_order(int cols, unsigned lanes, unsigned long long out, unsigned rows) {
     return gj::write_in_order(cols, lanes, out, rows);
 }
+extern "C" int stage(int cols, unsigned long long out, unsigned long long s_rows) {
+    return gj::stage_payloads(cols, out, s_rows);
+}
+extern "C" int fits(unsigned long long lds, int waves) { return gj::staging_fits(lds, waves); }
 """
 
 
@@ -26,6 +31,8 @@ def rule(tmp_path_factory):
                     str(so)], check=True)
     L = ctypes.CDLL(str(so))
     L.in_order.argtypes = [ctypes.c_int, ctypes.c_uint, ctypes.c_ulonglong, ctypes.c_uint]
+    L.stage.argtypes = [ctypes.c_int, ctypes.c_ulonglong, ctypes.c_ulonglong]
+    L.fits.argtypes = [ctypes.c_ulonglong, ctypes.c_int]
     return L
 
 
@@ -49,3 +56,14 @@ def test_faster_side(rule, cols, matches, share, want):
 def test_ends(rule):
     assert not rule.in_order(8, 0, 0, 0) and not rule.in_order(8, 0, 2048, 2048)
     assert rule.in_order(8, 64, 2 ** 40, 2 ** 32 - 1) == 0 and rule.in_order(8, 64, 2 ** 40, 65536) == 1
+
+
+@pytest.mark.parametrize("waves,most", [(4, 160 * 1024 // 3), (8, 80 * 1024), (16, 156 * 1024)])
+def test_staging_leaves_twelve_waves(rule, waves, most):
+    assert rule.fits(most, waves) and not rule.fits(most + 8, waves) and rule.fits(8192, waves)
+
+
+def test_staging_needs_output(rule):
+    n = 1 << 24
+    assert not rule.stage(2, 2 * n, n) and rule.stage(2, 3 * n, n) and rule.stage(2, 4 * n, n)
+    assert not rule.stage(4, n + n // 2000, n) and rule.stage(4, n + n // 100, n) and not rule.stage(16, n // 2, n)
