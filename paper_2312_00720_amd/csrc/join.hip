@@ -653,6 +653,65 @@ __device__ __forceinline__ void write_dups(const JoinArgs &a, const JoinLds<K> &
     }
 }
 
+// The same matches where some bucket is too long to sort: a bucket's rows are in input
+// order, other keys between them. The wave writes the matches of an S row with
+// kRowByWave or more by itself, 64 entries of the bucket at a time, consecutive output
+// rows together; each lane writes those of its own row otherwise. (Every lane its own: each
+// of the 16 waves of a unit wrote to 64 places at once. 2^16 x 2^20 rows, 64 matches each,
+// one, two and eight payloads a side, write pass: 2777 -> 535, 4913 -> 828, 25029 -> 2742 us;
+// units of four waves took 1936, 4217 and 19942.)
+constexpr uint32_t kRowByWave = 8;
+template <typename K>
+__device__ __forceinline__ void write_long(const JoinArgs &a, const JoinLds<K> &sh, uint32_t r0, uint32_t s0, uint32_t ws,
+                                           uint32_t we, int skip_bits, int log2nb, uint64_t outpos) {
+    const int lane = lane_id();
+    const K *__restrict__ skey = static_cast<const K *>(a.skey) + s0;
+    K *__restrict__ tkey = static_cast<K *>(a.tkey);
+    const auto write = [&](uint32_t e, K key, uint64_t p, uint64_t sr) {
+        const uint32_t ri = r0 + sh.entry[e];
+        const uint64_t rr = a.rrow ? (uint64_t)a.rrow[ri] : (uint64_t)ri;
+        tkey[p] = key;
+        for (int j = 0; j < a.nr; ++j) copy_val(a.tr[j], a.rw[j], p, a.rp[j], rr);
+        for (int j = 0; j < a.ns; ++j) copy_val(a.ts[j], a.sw[j], p, a.sp[j], sr);
+    };
+    for (uint32_t base = ws; base < we; base += kWave) {
+        const bool valid = base + lane < we;
+        const K key = valid ? skey[base + lane] : K(0);
+        const uint32_t b = bucket_of<K>(key, skip_bits, log2nb);
+        const uint32_t lo = sh.b[b], hi = sh.b[b + 1];
+        uint32_t c = 0;
+        if (valid)
+            for (uint32_t e = lo; e < hi; ++e) c += sh.rkey[e] == key ? 1u : 0u;
+        const uint32_t incl = wave_inclusive_sum<uint32_t>(c), ex = incl - c;
+        for (uint64_t rows = __ballot(c >= kRowByWave); rows; rows &= rows - 1) {
+            const int l = __ffsll((long long)rows) - 1;
+            const K k = __shfl(key, l, kWave);
+            const uint32_t si = s0 + base + l, end = __shfl(hi, l, kWave);
+            const uint64_t sr = a.srow ? (uint64_t)a.srow[si] : (uint64_t)si;
+            uint64_t first = outpos + __shfl(ex, l, kWave);
+            for (uint32_t e0 = __shfl(lo, l, kWave); e0 < end; e0 += kWave) {
+                const uint32_t e = e0 + lane;
+                const bool hit = e < end && sh.rkey[min(e, end - 1)] == k;
+                const uint64_t hits = __ballot(hit);
+                const uint64_t p = first + rank_below(hits);
+                if (hit && p < a.t_rows) write(e, k, p, sr);
+                first += (uint64_t)__popcll(hits);
+            }
+        }
+        if (c && c < kRowByWave) {
+            const uint32_t si = s0 + base + lane;
+            const uint64_t sr = a.srow ? (uint64_t)a.srow[si] : (uint64_t)si;
+            uint64_t p = outpos + ex;
+            for (uint32_t e = lo; e < hi; ++e) {
+                if (sh.rkey[e] != key || p >= a.t_rows) continue;
+                write(e, key, p, sr);
+                ++p;
+            }
+        }
+        outpos += __builtin_amdgcn_readlane(incl, kWave - 1);
+    }
+}
+
 // Write pass of unit u on the LDS table (the general case: partitions spanning
 // several R blocks, or S rows with several matches): build with chains in row
 // order, probe, and write every match at the positions the count pass sized.
@@ -776,7 +835,6 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
     // ---- probe: each wave streams a contiguous share of the S piece, PB
     // rounds of 64 rows at a time so that many loads are in flight ----
     const K *__restrict__ skey = static_cast<const K *>(a.skey);
-    in_order = in_order && !s_long;
     uint8_t *s_pay = reinterpret_cast<uint8_t *>(sh.is_long) + 8;
     int staged = 0;
     if (s_in_order && !s_long) {
@@ -797,7 +855,9 @@ __device__ __forceinline__ void write_unit(const JoinArgs &a, uint32_t u, uint64
         }
         __syncthreads();
     }
-    if (in_order) {
+    if (in_order && s_long) {
+        write_long<K>(a, sh, r0, s0, ws, we, skip_bits, log2nb, out_base + a.woff[(uint64_t)u * kWv + w]);
+    } else if (in_order) {
         write_dups<K>(a, sh, s_pay, staged, r0, s0, ws, we, skip_bits, log2nb, out_base + a.woff[(uint64_t)u * kWv + w]);
     } else {
         uint64_t outpos = out_base + a.woff[(uint64_t)u * kWv + w];

@@ -80,3 +80,32 @@ def test_plan_of_mixed_instances(cols, mat):
         assert len(got[0]) == len(want[0])
         for a, b in zip(got, want):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("mat", ["gftr", "gfur"])
+@pytest.mark.parametrize("kb,c_r,c_s,n_s", [(4, 2, 2, 3000), (8, 3, 1, 3000), (4, 1, 1, 3000), (4, 4, 4, 70000)])
+def test_long_buckets(kb, c_r, c_s, n_s, mat):
+    """Keys with 1 to 9, 63 to 65, 128 and 200 rows in one unit: rows written by a lane and
+    by the wave, in one and in several steps of 64 entries, beside each other."""
+    import paper_2312_00720_amd as gj
+    from gpu_util import dev, host, say
+    say(f"join long buckets {kb} {c_r} {c_s} {n_s} {mat}")
+    g = datagen.rng(kb + n_s)
+    reps = np.array([1, 2, 7, 8, 9, 63, 64, 65, 128, 200] + [1] * 300)
+    keys = g.permutation(4 * len(reps))[:len(reps)].astype(np.int64)
+    odd = 1 if kb == 4 else 0x5DEECE66D
+    dt = np.int32 if kb == 4 else np.int64
+    rk = (g.permutation(np.repeat(keys, reps)) * odd).astype(dt)
+    few = g.integers(0, len(reps), size=n_s)
+    few[g.random(n_s) < 0.9] = 20  # most S rows match one row, so that the result stays small
+    sk = (np.where(g.random(n_s) < 0.3, 4 * len(reps) + 1, keys[few]) * odd).astype(dt)
+    cols = lambda n, c: [g.integers(-2**62, 2**62, size=n, dtype=np.int64) if j % 2 == 1
+                         else g.integers(-2**31, 2**31, size=n, dtype=np.int64).astype(np.int32) for j in range(c)]
+    rp, sp = cols(len(rk), c_r), cols(n_s, c_s)
+    k, r, s = gj.join(dev(rk), [dev(x) for x in rp], dev(sk), [dev(x) for x in sp], mat=mat, algo="phj", radix_bits=1)
+    got = [host(k)] + [host(x) for x in r + s]
+    want = oracle.join(rk, rp, sk, sp)
+    order = np.argsort(want[0].astype(np.int64) & 1, kind="stable")
+    assert len(got[0]) == len(order) > 0
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(a, np.asarray(b)[order])
