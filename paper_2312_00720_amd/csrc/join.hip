@@ -1321,7 +1321,12 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
     // (else the pass runs again, sized exactly). A join of 2^16 x 2^20 rows waits
     // once instead of twice: 142 -> 130 us (1000 x 4000 rows: 112 -> 90). Larger tables keep the first read: their
     // LDS decides how many workgroups share a compute unit, and it is under 1% of the join.
-    bool guess = one_kernel && table_rows == 4096;
+    // Nor is there a guess where it cannot hold: partitions near the build block's rows,
+    // whose units the bound does not count (20000 x 2^22 rows, 2 partitions: the count pass ran
+    // for the bound and again, 71 us instead of 35).
+    const uint64_t guess_rows = (((uint64_t)R.rows >> bits) + 1) * 5 / 4;
+    bool guess = one_kernel && table_rows == 4096 && guess_rows <= (uint64_t)r_block;
+    bool units_known = false;
     uint32_t cap_units = (uint32_t)std::min<uint64_t>(bound, kMaxUnits), grid;
     uint32_t lds_rows = (uint32_t)r_block;  // rows of the largest R block a unit builds on
     uint32_t *umap = nullptr;
@@ -1379,12 +1384,13 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
             grid = std::max<uint32_t>(1, std::min<uint32_t>(cap_units, kPersistentGrid));
         } else if (guess) {
             grid = cap_units;
-            const uint32_t mean = (uint32_t)((uint64_t)R.rows >> bits) + 1;
-            lds_rows = std::min<uint32_t>((uint32_t)r_block, (mean + mean / 4 + 255) & ~255u);
+            lds_rows = std::min<uint32_t>((uint32_t)r_block, ((uint32_t)guess_rows + 255) & ~255u);
         } else {
             // eager calls read the unit count and size every launch exactly
-            read_back_parts(s, {{&units, nunits, 4}, {hf, flags, sizeof(hf)}});
-            if (!check_units()) return -1;
+            if (!units_known) {
+                read_back_parts(s, {{&units, nunits, 4}, {hf, flags, sizeof(hf)}});
+                if (!check_units()) return -1;
+            }
             lds_rows = exact_rows();
             if (units == 0) {
                 if (inst_off) fill_u64(s, inst_off, 0ull, (uint64_t)n_inst + 1);
@@ -1421,6 +1427,7 @@ int64_t join_partitioned(Ctx &ctx, int key_bytes, const JoinSide &R, const JoinS
             if (!check_units()) return -1;
             if (units > cap_units || std::min<uint32_t>(hf[2], (uint32_t)r_block) > lds_rows) {
                 guess = false;  // the bounds did not hold: nothing is known but the units
+                units_known = true;
                 continue;
             }
             if (units == 0) return 0;
