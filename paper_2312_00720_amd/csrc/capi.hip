@@ -46,7 +46,7 @@ gj::PassCounts gb_chunks(uint32_t n, int kb, int n_vals, const int *width, bool 
         row += (uint32_t)width[i];
         narrow = narrow && width[i] == 4;
     }
-    return gj::pass_chunks(n, row, narrow);
+    return gj::pass_chunks(n, kb, row, narrow);
 }
 
 void check_rel(const gj_rel *r, const char *what) {

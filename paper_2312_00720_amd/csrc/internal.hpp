@@ -13,6 +13,7 @@
 
 #include "../../include/gj.h"
 #include "common.hpp"
+#include "scatter_rule.hpp"
 
 namespace gj {
 
@@ -217,6 +218,7 @@ struct PassCounts {
     const uint32_t *hist8 = nullptr;
     uint32_t chunk_rows = 0;
     bool cells = false;  // long chunks
+    TileShape tile{};    // of a pass in short ones
 };
 void partition_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, const PartCols &cols,
                    uint32_t n, int bit_lo, int bits, int passes, int mode, uint32_t *poff,
@@ -224,7 +226,7 @@ void partition_run(Ctx &ctx, int key_bytes, const void *key_in, void *key_out, c
 // The chunks (hist8 not set) for counts that are made before the digit bits are known:
 // those of a pass by 8 bits over one segment of n rows of row_bytes bytes (key and
 // columns; narrow: all 4 bytes wide) with the current scatter shape.
-PassCounts pass_chunks(uint32_t n, uint32_t row_bytes, bool narrow);
+PassCounts pass_chunks(uint32_t n, int key_bytes, uint32_t row_bytes, bool narrow);
 
 // One stable pass over nseg segments (device offsets seg_off[0..nseg]), the digit of
 // segment s being the low seg_bits[s] (<= 8) bits of the digit source `mode` (the key

@@ -26,7 +26,6 @@
 #include <vector>
 
 #include "internal.hpp"
-#include "scatter_rule.hpp"
 
 namespace gj {
 namespace {
@@ -1166,9 +1165,7 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_scatter(PassArgs a) {
 
 // Scatter tile shapes (rows per thread x 4-byte columns loaded together). The
 // shape changes speed only; GJ_SCATTER_SHAPE=<items>x<group> picks one.
-struct Shape {
-    int block, items, group;
-};
+using Shape = TileShape;
 // Group 0 is the wide-tile kernel (one column at a time, rolling prefetch).
 constexpr Shape kVariants[kScatterVariants] = {{256, 8, 4},  {512, 8, 4},  {1024, 8, 4}, {512, 4, 4},
                                                {1024, 4, 4}, {256, 16, 2}, {512, 8, 2},  {512, 16, 2},
@@ -1189,18 +1186,10 @@ Shape scatter_shape() {
     return sh;
 }
 
-// The shape of a pass over n rows in nseg segments. Where no shape was asked
-// for, tiles shrink with the input so that they still fill the chip: scatter of
-// key + column by 5 bits, 2^18 rows: 18.3 us in 16384-row tiles, 9.1 in
-// 2048-row ones; 2^20 rows: 19.7 and 11.7 us; 2^22 rows 33 us, 30 in 4096-row
-// tiles (with four columns 46 and 42); 2^23 rows with four columns: 85 and 89 us.
-Shape pass_shape(uint32_t n, uint32_t nseg) {
+// The shape of a pass over n rows in nseg segments: the one asked for, else tile_shape's.
+Shape pass_shape(uint32_t n, uint32_t nseg, int bits, int key_bytes, uint32_t row_bytes, bool narrow) {
     const Shape sh = scatter_shape();
-    if (sh.group >= 0) return sh;
-    const uint32_t avg = n / (nseg > kRadix ? nseg : 1);  // a batch's tiles end with its instances
-    if (n <= 1u << 20 || avg <= 4096) return Shape{512, 4, 4};
-    if (n <= 3u << 21 || avg <= 16384) return Shape{512, 8, 4};
-    return sh;
+    return sh.group >= 0 ? sh : tile_shape(n, nseg, bits, key_bytes, row_bytes, narrow);
 }
 
 // The whole-line kernel's launch for a pass of shape sh (line_shape).
@@ -1295,9 +1284,8 @@ __global__ __launch_bounds__(256) void k_key_bits(const K *__restrict__ keys, ui
 // Rows per chunk: long ones, one for each of the 256 compute units (chunks share
 // lines at their ends: 2^27 rows, 7 bits: 1.12 ms with 256 chunks, 1.20 with
 // 1024); else one tile, at most ~4096 chunks.
-uint32_t chunk_rows_for(uint32_t n, uint32_t nseg, bool cells) {
+uint32_t chunk_rows_for(uint32_t n, const Shape &sh, bool cells) {
     if (cells) return ceil_div_u32(ceil_div_u32(n, 256), 1024) * 1024;
-    const Shape sh = pass_shape(n, nseg);
     const uint32_t tile = (uint32_t)(sh.block * sh.items);
     const uint32_t tiles = ceil_div_u32(n, tile);
     const uint32_t per = tiles > 4096 ? ceil_div_u32(tiles, 4096) : 1;
@@ -1325,9 +1313,9 @@ void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const PassCounts *counts = null
     for (int c = 0; c < a.ncols; ++c) at |= (uintptr_t)a.col_out[c];
     const bool aligned = (at & 15u) == 0;
     a.cells = counts ? counts->cells : long_chunks_for(n, a.nseg, a.bits, a.row_bytes, narrow, aligned);
-    a.chunk_rows = counts ? counts->chunk_rows : chunk_rows_for(n, a.nseg, a.cells);
+    const Shape sh = counts ? counts->tile : pass_shape(n, a.nseg, a.bits, (int)sizeof(K), a.row_bytes, narrow);
+    a.chunk_rows = counts ? counts->chunk_rows : chunk_rows_for(n, sh, a.cells);
     a.n_chunks = ceil_div_u32(n, a.chunk_rows);
-    const Shape sh = pass_shape(n, a.nseg);
     const uint64_t max_chunks = a.seg_off ? (uint64_t)a.n_chunks + a.nseg : a.n_chunks;
     // algorithmic bytes of one scatter: read and write the key and every column
     // once (a generated row id is only written)
@@ -1372,10 +1360,11 @@ void run_pass(Ctx &ctx, PassArgs &a, uint32_t n, const PassCounts *counts = null
 
 void set_scatter_variant(int v) { g_variant = v; }
 
-PassCounts pass_chunks(uint32_t n, uint32_t row_bytes, bool narrow) {
+PassCounts pass_chunks(uint32_t n, int key_bytes, uint32_t row_bytes, bool narrow) {
     PassCounts c;
+    c.tile = pass_shape(n, 1, 8, key_bytes, row_bytes, narrow);
     c.cells = long_chunks_for(n, 1, 8, row_bytes, narrow, true);
-    c.chunk_rows = chunk_rows_for(n, 1, c.cells);
+    c.chunk_rows = chunk_rows_for(n, c.tile, c.cells);
     return c;
 }
 

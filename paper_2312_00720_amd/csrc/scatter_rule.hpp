@@ -1,4 +1,4 @@
-// Which scatter a partition pass takes: sizes and limits only, host code without
+// Which scatter and which tiles a partition pass takes: sizes and limits only, host code without
 // HIP, so that the rule can be checked on its own.
 #pragma once
 
@@ -17,6 +17,44 @@ constexpr size_t line_lds_bytes(uint32_t D, uint32_t A, uint32_t row_bytes, uint
     return (size_t)line_max(D, A, tile) * A * w + (size_t)D * A * row_bytes + align16((size_t)kLineWaves * D * 2) +
            align16((size_t)D * 4) + (size_t)D * 16 + align16((size_t)(D + 1) * 2) + align16(line_max(D, A, tile)) +
            4 * kLineWaves;
+}
+
+// Tiles of a pass in short chunks: threads, rows per thread, 4-byte columns loaded
+// together (0: the wide kernel, one column at a time).
+struct TileShape {
+    int block, items, group;
+};
+constexpr TileShape kWideTile{1024, 16, 0}, kTile4096{512, 8, 4}, kTile2048{512, 4, 4};
+// Tiles shrink with the input so that they still fill the chip. All kernels of a
+// partition, 2048-row tiles : 4096-row tiles : wide, us.
+//  - Up to 2^20 rows the small ones; 8 bytes a row, 5 bits, 2^20: 30 : 33 : 42.
+//  - 8-byte keys: the 4096-row tiles lose to both others past 2^20 (12 bytes a row, 5 bits, 2^22: 56
+//    : 70 : 54; 24 bytes, 8 + 5 bits, 6.2M: 237 : 299 : 260).
+//  - 4-byte keys, to 2.6M rows the 4096-row tiles (20 bytes, 8 bits, 2^21: 72 : 62 : 67).
+//  - Up to three bits: runs are long, and the wide kernel is ahead from there on, and
+//    from 2^21 with 8-byte keys (20 bytes, 2 bits, 2^22: 100 : 76 : 62; 6.2M: 182 : 132 : 87; 24 bytes
+//    with 8-byte keys 193 : 195 : 111).
+//  - To 2^22 rows, whose wide tiles run in one round of the 256 compute units, the wide
+//    kernel (20 bytes, 8 bits, 2^22: 102 : 90 : 81), but not over segments of narrow rows,
+//    which end in part of a tile (8 + 5 bits, 2.9M: 4 bytes 95 : 96 : 100, 20 bytes with 8-byte
+//    columns 123 : 124 : 136, 20 bytes of 4-byte columns 140 : 146 : 137).
+//  - Past it the second round is nearly empty: the 4096-row tiles to 5.8M rows (5.0M, 8 bits: 8 bytes
+//    73 : 70 : 77, 20 bytes with 8-byte columns 94 : 88 : 104) unless rows are wide (36 bytes 225 : 187 :
+//    175; 68 bytes with 8-byte columns 355 : 304 : 273, but by 5 bits 226 : 206 : 228).
+//  - Many segments (a batch): tiles end with its instances.
+constexpr TileShape tile_shape(uint64_t n, uint32_t nseg, int bits, int key_bytes, uint32_t row_bytes, bool narrow) {
+    if (nseg > 256) {
+        if (n <= 1u << 20 || n / nseg <= 4096) return kTile2048;
+        return n <= 3u << 21 || n / nseg <= 16384 ? kTile4096 : kWideTile;
+    }
+    if (n <= 1u << 20) return kTile2048;
+    if (key_bytes == 8) return n <= (bits <= 3 ? 1u << 21 : 3u << 21) ? kTile2048 : kWideTile;
+    if (n <= 5u << 19) return kTile4096;
+    const bool second = n > 1u << 22 && n <= 11u << 19;  // wide tiles: a nearly empty round
+    if (second && !narrow && row_bytes > 32 && bits <= 5) return kTile4096;
+    if (bits <= 3) return kWideTile;
+    if (n <= 1u << 22) return nseg > 1 && row_bytes < (narrow ? 12u : 32u) ? kTile4096 : kWideTile;
+    return (second || (!narrow && n <= 3u << 21)) && row_bytes <= 32 ? kTile4096 : kWideTile;
 }
 
 // The whole-line kernel's shape for a pass of `bits` digit bits: lines of 32 rows
