@@ -1526,6 +1526,31 @@ __global__ __launch_bounds__(kBlock) void k_hgb_insert(HgbArgs a) {
     }
 }
 
+// Rows inserted ahead of a pass over all rows, which then writes every gid_loc. Many
+// workgroups meet on few slots here, so a lane whose key one of the wave's first 16
+// distinct ones is, and an earlier lane's, leaves the insert to that lane (2^20 rows, one group,
+// 5461 rows ahead: both inserts 72 us with every lane inserting).
+template <typename K>
+__global__ __launch_bounds__(kBlock) void k_hgb_insert_ahead(HgbArgs a) {
+    const K *__restrict__ keys = static_cast<const K *>(a.keys);
+    const uint64_t mask = (1ull << a.log2cap) - 1ull;
+    const int lane = lane_id();
+    for (uint32_t base = blockIdx.x * kBlock; base < a.n; base += gridDim.x * kBlock) {
+        const uint32_t i = base + threadIdx.x;
+        const bool valid = i < a.n;
+        const K k = valid ? keys[i] : K(0);
+        bool keep = valid;
+        uint64_t rest = __ballot(valid);
+        for (int t = 0; t < 16 && rest; ++t) {
+            const int l = __ffsll((long long)rest) - 1;
+            const bool same = valid && k == __shfl(k, l, kWave);
+            keep = keep && (!same || lane == l);
+            rest &= ~__ballot(same);
+        }
+        if (keep) hgb_insert_from<K, false>(a, keys, i, k, global_slot_hash<K>(k) & mask);
+    }
+}
+
 // Stage 1 for 4-byte keys and a few thousand groups: each workgroup keeps the
 // keys it has resolved, with their gid_loc, in an LDS table (Fibonacci hashing,
 // linear probing over at most kCacheProbe slots), so that a row whose key the
@@ -2666,12 +2691,13 @@ void groupby_partition_segments(Ctx &ctx, int key_bytes, const void *key, const 
 
 // Stage 1 of Algorithm 1: dense group ids from a global table. Fills a.gid (for
 // the inserting rows), a.gid_loc, a.tmp_keys (the key of each id) and returns
-// the group count. One workgroup first inserts the first `prefix` rows a tile at
-// a time, so that the keys seen there take the lowest ids (see groupby_hash).
+// the group count. The first `prefix` rows go in first: by one workgroup a tile at a
+// time, so that the keys seen there take the lowest ids (see groupby_hash), or, with
+// any_order and a few thousand groups, by many.
 // The table: 1.5 slots per row always holds every group; with a group-count
 // estimate it is sized for that instead (load `occupancy`, default 0.45), and a
 // row that finds no slot within 4096 probes sends the insert back to the
-// row-sized table. any_order: ids need not follow the rows.
+// row-sized table.
 static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *key, uint32_t n, uint32_t prefix,
                         double g_est, float occupancy, bool any_order) {
     hipStream_t st = ctx.stream;
@@ -2684,10 +2710,15 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
     a.tmp_keys = ctx.scratch((size_t)n * key_bytes);
     // Where the order of the ids does not matter and the cached kernels follow, the
     // prefix only has to fill the table that they copy: many workgroups, 16 rows per
-    // group. What it misses, every workgroup of the full pass looks up on its own.
-    const bool spread = any_order && g_est > 0.0 && g_est <= (key_bytes == 4 ? 6144.0 : 3072.0);
+    // group. What it misses, the first rounds of all workgroups of the full pass look up
+    // (2^24 rows, 15 skewed groups of which 256 rows missed one: both inserts 163 us, 32
+    // with 5461), so it grows with their number, up to the rows that one workgroup takes.
     // Up to 2048 rows it takes them all, and there is no full pass to launch.
-    if (spread) prefix = std::max<uint32_t>(n <= 2048 ? 2048u : (uint32_t)kBlock, (uint32_t)(g_est * 16.0));
+    const bool spread = any_order && g_est > 0.0 && g_est <= (key_bytes == 4 ? 6144.0 : 3072.0);
+    if (spread) {
+        const uint32_t by_groups = (uint32_t)(g_est * 16.0);
+        prefix = std::max(by_groups, n <= 2048 ? n : std::min(prefix, std::max<uint32_t>(kBlock, n >> 8)));
+    }
     prefix = std::min(prefix, n);
     const uint32_t grid = std::min<uint32_t>(ceil_div_u32(n, kBlock), 256u * 16u);
     int log2rows = 4;
@@ -2701,10 +2732,15 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
         fill_u32(st, a.ngroups, 0u, 2);
         HgbArgs ap = a;
         ap.n = prefix;
-        const uint32_t pblocks = spread ? ceil_div_u32(prefix, kBlock) : 1;
         if (key_bytes == 4) {
-            GJ_LAUNCH("k_hgb_insert", 8.0 * prefix, (k_hgb_insert<int32_t, 1>), dim3(pblocks), dim3(kBlock), 0,
-                      st, ap);
+            if (spread && prefix < n)
+                GJ_LAUNCH("k_hgb_insert", 8.0 * prefix, k_hgb_insert_ahead<int32_t>, dim3(ceil_div_u32(prefix, kBlock)),
+                          dim3(kBlock), 0, st, ap);
+            else if (spread)
+                GJ_LAUNCH("k_hgb_insert", 8.0 * prefix, (k_hgb_insert<int32_t, 1>), dim3(ceil_div_u32(prefix, kBlock)),
+                          dim3(kBlock), 0, st, ap);
+            else
+                GJ_LAUNCH("k_hgb_insert", 8.0 * prefix, (k_hgb_insert<int32_t, 16>), dim3(1), dim3(kBlock), 0, st, ap);
             if (n > prefix) {
                 // up to a few thousand groups: every workgroup caches the keys it
                 // resolved (an 8192-entry LDS table, at most three quarters full)
@@ -2716,8 +2752,14 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
                     GJ_LAUNCH("k_hgb_insert", 8.0 * n, (k_hgb_insert<int32_t, 16>), dim3(grid), dim3(kBlock), 0, st, a);
             }
         } else {
-            GJ_LAUNCH("k_hgb_insert", 12.0 * prefix, (k_hgb_insert<int64_t, 1>), dim3(pblocks), dim3(kBlock), 0,
-                      st, ap);
+            if (spread && prefix < n)
+                GJ_LAUNCH("k_hgb_insert", 12.0 * prefix, k_hgb_insert_ahead<int64_t>, dim3(ceil_div_u32(prefix, kBlock)),
+                          dim3(kBlock), 0, st, ap);
+            else if (spread)
+                GJ_LAUNCH("k_hgb_insert", 12.0 * prefix, (k_hgb_insert<int64_t, 1>), dim3(ceil_div_u32(prefix, kBlock)),
+                          dim3(kBlock), 0, st, ap);
+            else
+                GJ_LAUNCH("k_hgb_insert", 12.0 * prefix, (k_hgb_insert<int64_t, 16>), dim3(1), dim3(kBlock), 0, st, ap);
             if (n > prefix) {
                 // up to a few thousand groups: a 4096-entry LDS cache per workgroup
                 if (g_est > 0.0 && g_est <= 3072.0 && ((uintptr_t)key & 15u) == 0 && ((uintptr_t)a.gid_loc & 15u) == 0)
@@ -2751,11 +2793,13 @@ int64_t groupby_hash(Ctx &ctx, int key_bytes, const void *key, const ValCols &vc
     HgbArgs a{};
     const uint32_t grid = std::min<uint32_t>(ceil_div_u32(n, kBlock), 256u * 16u);
     // Group ids come from an atomic counter, so a full grid hands them out in the
-    // order its first tiles happen to win, unrelated to key frequency. One
+    // order its first tiles happen to win, unrelated to key frequency. Where an LDS
+    // budget may leave groups without a record in LDS, or there are many groups, one
     // workgroup first inserts a prefix of the rows a tile at a time: the keys seen
     // there take the low ids, and under skew those are the frequent keys. Low ids
-    // are the ones that keep LDS records when not every group fits. The full pass
-    // then finds the prefix keys already present.
+    // are the ones that keep LDS records when not every group fits. A few thousand
+    // groups all fit, so there the order does not matter. The full pass then finds the
+    // prefix keys already present.
     const int n_vals = vc.n;
     std::vector<void *> no_outs(n_aggs, nullptr);
     const size_t rec_even = (size_t)make_spec(aggs, n_aggs, no_outs.data(), vc.width, false).words * 4;
