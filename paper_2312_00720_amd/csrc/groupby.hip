@@ -2720,6 +2720,7 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
         prefix = std::max(by_groups, n <= 2048 ? n : std::min(prefix, std::max<uint32_t>(kBlock, n >> 8)));
     }
     prefix = std::min(prefix, n);
+    const bool ahead = spread && prefix < n && prefix > (uint32_t)kBlock;  // one workgroup does not contend
     const uint32_t grid = std::min<uint32_t>(ceil_div_u32(n, kBlock), 256u * 16u);
     int log2rows = 4;
     while ((1ull << log2rows) < (uint64_t)n + n / 2) ++log2rows;
@@ -2733,7 +2734,7 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
         HgbArgs ap = a;
         ap.n = prefix;
         if (key_bytes == 4) {
-            if (spread && prefix < n)
+            if (ahead)
                 GJ_LAUNCH("k_hgb_insert", 8.0 * prefix, k_hgb_insert_ahead<int32_t>, dim3(ceil_div_u32(prefix, kBlock)),
                           dim3(kBlock), 0, st, ap);
             else if (spread)
@@ -2752,7 +2753,7 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
                     GJ_LAUNCH("k_hgb_insert", 8.0 * n, (k_hgb_insert<int32_t, 16>), dim3(grid), dim3(kBlock), 0, st, a);
             }
         } else {
-            if (spread && prefix < n)
+            if (ahead)
                 GJ_LAUNCH("k_hgb_insert", 12.0 * prefix, k_hgb_insert_ahead<int64_t>, dim3(ceil_div_u32(prefix, kBlock)),
                           dim3(kBlock), 0, st, ap);
             else if (spread)
