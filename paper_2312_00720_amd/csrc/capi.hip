@@ -442,7 +442,9 @@ int gj_groupby(gj_col key, const gj_col *vals, int32_t n_vals, int64_t n_rows, c
         }
 
         gj::Ctx ctx(alloc, (hipStream_t)stream);
-        ctx.expect((uint64_t)n * kb);  // every algorithm holds the keys once more
+        // every algorithm holds the keys once more, and the values or row ids, or two words a row
+        const uint64_t val_row = copied_bytes(1, 0, vals, n_vals, gfur);
+        ctx.expect((uint64_t)n * ((uint64_t)kb + std::min<uint64_t>(val_row, 8)));
         // the group count decides the algorithm and the partition passes: estimate it
         double g_est = 0.0;
         int varying = 0;
