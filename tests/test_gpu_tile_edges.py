@@ -44,3 +44,21 @@ def test_group_by(n, groups, key64):
     assert torch.equal(cnt[order], torch.bincount(idx, minlength=groups))
     want = torch.zeros(groups, dtype=torch.int64, device="cuda").index_add_(0, idx, val.to(torch.int64))
     assert torch.equal(tot[order], want)
+
+
+@pytest.mark.parametrize("n,rows", [(1 << 20, 2048), ((1 << 20) + 1, 4096), (1 << 22, 4096), ((3 << 21) + 1, 16384)])
+def test_sketch_chunks(n, rows):
+    """8-byte keys: the sketch's workgroups count 4096 rows at least from 2^20 rows, from the bytes
+    of the fold that follows them (256 counts in, 2^bits out for every chunk)."""
+    import torch
+    import paper_2312_00720_amd as gj
+    print(f"sketch chunks n={n}", flush=True)
+    idx = torch.arange(n, device="cuda") * 7919 % 400
+    val = torch.arange(n, device="cuda", dtype=torch.int32)
+    gj.profile_start()
+    k, (cnt,) = gj.groupby(idx * 0x5DEECE66D, [val], [(0, "count")], algo="partition")
+    torch.cuda.synchronize()
+    p = gj.profile_stop()
+    chunks = -(-n // rows)
+    assert p["k_fold_hist"]["alg_bytes"] in [4.0 * chunks * (256 + (1 << b)) for b in range(1, 9)]
+    assert torch.equal(cnt[torch.argsort(k)], torch.bincount(idx))
