@@ -2720,7 +2720,8 @@ static uint32_t hgb_assign_ids(Ctx &ctx, HgbArgs &a, int key_bytes, const void *
         prefix = std::max(by_groups, n <= 2048 ? n : std::min(prefix, std::max<uint32_t>(kBlock, n >> 8)));
     }
     prefix = std::min(prefix, n);
-    const bool ahead = spread && prefix < n && prefix > (uint32_t)kBlock;  // one workgroup does not contend
+    // one workgroup does not contend, nor do many groups (2^20 rows, 1000: 2 us for nothing)
+    const bool ahead = spread && prefix < n && prefix > (uint32_t)kBlock && g_est <= 64.0;
     const uint32_t grid = std::min<uint32_t>(ceil_div_u32(n, kBlock), 256u * 16u);
     int log2rows = 4;
     while ((1ull << log2rows) < (uint64_t)n + n / 2) ++log2rows;
