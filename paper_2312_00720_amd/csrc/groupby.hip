@@ -2420,6 +2420,11 @@ double estimate_groups(Ctx &ctx, int key_bytes, const void *key, uint32_t n, int
     return std::min(e, (double)n);
 }
 
+// Bytes discovery reads: the keys twice, once where the mean partition is small enough.
+static double discover_bytes(int key_bytes, uint32_t n, uint32_t np) {
+    return (n / np <= kDiscoverCap / 2 ? 1.0 : 2.0) * (double)key_bytes * n;
+}
+
 static const uint32_t *pgb_unit_map(Ctx &ctx, const uint32_t *ubase, uint32_t np, uint32_t cap) {
     uint32_t *umap = ctx.scratch_n<uint32_t>(std::max<uint32_t>(cap, 1));
     GJ_LAUNCH("k_pgb_unit_map", 4.0 * cap, k_pgb_unit_map,
@@ -2474,11 +2479,11 @@ int64_t groupby_partition(Ctx &ctx, int key_bytes, const void *key, const ValCol
     // the two discovery kernels (partitions up to kDiscoverUnit rows, and slices of
     // larger ones) share one tag: together they read the keys twice
     if (key_bytes == 4) {
-        GJ_LAUNCH("k_pgb_discover", 8.0 * n, k_pgb_discover<int32_t>, dim3(np), dim3(kBlock), 0, st, a);
+        GJ_LAUNCH("k_pgb_discover", discover_bytes(key_bytes, n, np), k_pgb_discover<int32_t>, dim3(np), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_discover", 0.0, k_pgb_discover_unit<int32_t>, dim3(max_du), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_merge", 8.0 * np, k_pgb_merge<int32_t>, dim3(max_du), dim3(kBlock), 0, st, a);
     } else {
-        GJ_LAUNCH("k_pgb_discover", 16.0 * n, k_pgb_discover<int64_t>, dim3(np), dim3(kBlock), 0, st, a);
+        GJ_LAUNCH("k_pgb_discover", discover_bytes(key_bytes, n, np), k_pgb_discover<int64_t>, dim3(np), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_discover", 0.0, k_pgb_discover_unit<int64_t>, dim3(max_du), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_merge", 16.0 * np, k_pgb_merge<int64_t>, dim3(max_du), dim3(kBlock), 0, st, a);
     }
@@ -2613,11 +2618,11 @@ void groupby_partition_segments(Ctx &ctx, int key_bytes, const void *key, const 
     // the two discovery kernels (partitions up to kDiscoverUnit rows, and slices of
     // larger ones) share one tag: together they read the keys twice
     if (key_bytes == 4) {
-        GJ_LAUNCH("k_pgb_discover", 8.0 * n, k_pgb_discover<int32_t>, dim3(np), dim3(kBlock), 0, st, a);
+        GJ_LAUNCH("k_pgb_discover", discover_bytes(key_bytes, n, np), k_pgb_discover<int32_t>, dim3(np), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_discover", 0.0, k_pgb_discover_unit<int32_t>, dim3(max_du), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_merge", 8.0 * np, k_pgb_merge<int32_t>, dim3(max_du), dim3(kBlock), 0, st, a);
     } else {
-        GJ_LAUNCH("k_pgb_discover", 16.0 * n, k_pgb_discover<int64_t>, dim3(np), dim3(kBlock), 0, st, a);
+        GJ_LAUNCH("k_pgb_discover", discover_bytes(key_bytes, n, np), k_pgb_discover<int64_t>, dim3(np), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_discover", 0.0, k_pgb_discover_unit<int64_t>, dim3(max_du), dim3(kBlock), 0, st, a);
         GJ_LAUNCH("k_pgb_merge", 16.0 * np, k_pgb_merge<int64_t>, dim3(max_du), dim3(kBlock), 0, st, a);
     }

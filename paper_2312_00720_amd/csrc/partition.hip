@@ -30,13 +30,12 @@
 namespace gj {
 namespace {
 
-// Default scatter shape: 1024 threads x 16 rows, the whole-line kernel for large
-// passes (long_chunks) and the wide kernel (one column at a time with a rolling
-// prefetch) otherwise; group 0 names the wide kernel among the shapes.
+// Default scatter: the whole-line kernel for large passes (long_chunks), else the
+// tiles of tile_shape. Group 0 names the wide kernel among the shapes (one column at
+// a time with a rolling prefetch).
 constexpr int kScatterBlock = 1024;
 constexpr int kItems = 16;
 constexpr int kGroup = -1;
-constexpr uint32_t kTile = kBlock * kItems;
 
 // Where a chunk's output offsets come from: the scanned counts (hist), the raw
 // counts of its segment, or the tile itself (the input is one tile).
