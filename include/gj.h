@@ -16,8 +16,8 @@
  *     before the call returns, in stream order (the caller's allocator must be
  *     stream-ordered, as a caching device allocator on `stream` is). Small
  *     scratch shares requests of at most 256 KB, none of them larger than
- *     4 KB, or than the copies of its input that the call makes in any case,
- *     or than a quarter of what it was given so far. A NULL allocator means
+ *     4 KB, or than the scratch that the call takes in any case, or than a
+ *     quarter of what it was given so far. A NULL allocator means
  *     hipMallocAsync/hipFreeAsync on `stream`.
  *   - Row counts are at most 2^31 - 1 per relation (row identifiers are
  *     32-bit); larger inputs return GJ_EOVERFLOW.

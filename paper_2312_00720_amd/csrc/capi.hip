@@ -167,8 +167,9 @@ int gj_join(const gj_rel *R, const gj_rel *S, const gj_join_opts *opts, const gj
         gj::Ctx ctx(alloc, (hipStream_t)stream);
         gj::JoinSide side[2];
         const gj_rel *rel[2] = {R, S};
+        // the copies, two bytes or more of match per S row, and some twenty pieces of a few words
         ctx.expect(copied_bytes(R->n_rows, kb, R->payloads, R->n_payloads, gfur) +
-                   copied_bytes(S->n_rows, kb, S->payloads, S->n_payloads, gfur));
+                   copied_bytes(S->n_rows, kb, S->payloads, S->n_payloads, gfur) + 2ull * (uint64_t)S->n_rows + 20 * 256);
         if (o.algo == GJ_JOIN_SMJ) {
             // transformation: full-key LSD radix sort of (key, payloads) or (key, row id)
             for (int t = 0; t < 2; ++t) {
